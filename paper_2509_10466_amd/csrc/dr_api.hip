@@ -385,7 +385,10 @@ static dr_status run_blocks(dr_ctx* c, const Geo& g, dr_precision prec, hipStrea
       LAUNCH(ST_LN1, launch_ln_f32(w.x, nullptr, nullptr, N, C, b.ln1g, b.ln1b, w.u, s));
       LAUNCH(ST_QKV, launch_gemm_f32(w.u, nullptr, nullptr, N, C, b.wkv, b.bkv, 2 * C, EPI_STORE, w.kv, nullptr, s));
       LAUNCH(ST_QKV, launch_gemm_f32(w.u, w.idx, w.nq, N, C, b.wq, b.bq, C, EPI_STORE, w.q, nullptr, s));
-      LAUNCH(ST_ATTN, launch_attn_f32(g, C, n.cfg.heads, w.q, w.kv, w.woff, w.o, s));
+      if (attn_train_supported(n.dh, g.S))
+        LAUNCH(ST_ATTN, launch_attn_train_fwd(g, C, n.cfg.heads, w.q, w.kv, w.woff, w.o, nullptr, s));
+      else
+        LAUNCH(ST_ATTN, launch_attn_f32(g, C, n.cfg.heads, w.q, w.kv, w.woff, w.o, s));
       LAUNCH(ST_PROJ, launch_gemm_f32(w.o, nullptr, w.nq, N, C, b.wo, b.bo, C, EPI_RESID, w.x, w.idx, s));
       LAUNCH(ST_LN2, launch_ln_f32(w.x, w.idx, w.nq, N, C, b.ln2g, b.ln2b, w.u, s));
       LAUNCH(ST_FC1, launch_gemm_f32(w.u, nullptr, w.nq, N, C, b.w1, b.b1, R, EPI_GELU, w.h, nullptr, s));

@@ -253,6 +253,17 @@ void launch_gemm_f32(const float* A, const int32_t* arows, const int32_t* m_dev,
                      const int32_t* res_rows, hipStream_t s);
 void launch_attn_f32(const Geo& g, int C, int heads, const float* q, const float* kv,
                      const int32_t* woff, float* o, hipStream_t s);
+// FP32 window attention on the matrix cores, with each query's and head's softmax (max, sum)
+// in stats unless that is null
+bool attn_train_supported(int dh, int S);
+void launch_attn_train_fwd(const Geo& g, int C, int heads, const float* q, const float* kv, const int32_t* woff,
+                           float* o, float2* stats, hipStream_t s);
+
+// Token reductions of the training passes: rows per partial
+constexpr int TN_CHUNK = 2048;  // weight gradients and column sums
+constexpr int LNB_ROWS = 64;    // LayerNorm gain and shift gradients
+inline int tn_chunks(int M_max) { return (M_max + TN_CHUNK - 1) / TN_CHUNK; }
+inline int ln_bwd_blocks(int n_max) { return (n_max + LNB_ROWS - 1) / LNB_ROWS; }
 
 // FP8 path (OCP e4m3 operands, per-tensor scales s = amax/448, FP32 accumulation)
 bool fp8_supported(int C, int R);

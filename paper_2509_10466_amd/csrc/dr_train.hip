@@ -22,19 +22,15 @@ void launch_gather_rows(const float* X, const int32_t* rows, const int32_t* n_de
 void launch_scatter_rows(const float* Y, const int32_t* rows, const int32_t* n_dev, int n_max, int C, float* X, hipStream_t s);
 void launch_gelu_fwd(const float* h, const int32_t* n_dev, int n_max, int R, float* a, hipStream_t s);
 void launch_gelu_bwd(const float* h, const float* da, const int32_t* n_dev, int n_max, int R, float* dh, hipStream_t s);
-bool attn_train_supported(int dh, int S);
-void launch_attn_train_fwd(const Geo& g, int C, int heads, const float* q, const float* kv, const int32_t* woff,
-                           float* o, float2* stats, hipStream_t s);
 void launch_attn_train_dq(const Geo& g, int C, int heads, const float* q, const float* kv, const float* dout,
                           const float2* stats, const int32_t* woff, float* dq, float* dsum, hipStream_t s);
 void launch_attn_train_dkv(const Geo& g, int C, int heads, const float* q, const float* kv, const float* dout,
                            const float2* stats, const float* dsum, const int32_t* woff, float* dkv, hipStream_t s);
 void launch_ln_bwd(const float* x, const int32_t* rows, const int32_t* n_dev, int n_max, int C, const float* g,
                    const float* dy, float* dx, int accumulate, int dst_compact, float* part, hipStream_t s);
-int ln_bwd_blocks(int n_max);
-void launch_sum_parts(const float* part, int nparts, int width, float* out, int accumulate, hipStream_t s);
-int tn_chunks(int M_max);
-void launch_tn_partial(const float* A, const int32_t* arow, int lda, const float* B, const int32_t* brow, int ldb,
+void launch_sum_parts(const float* part, int nparts, const int32_t* n_dev, int rows_per, int width, float* out,
+                      int accumulate, hipStream_t s);
+void launch_tn_f32(const float* A, const int32_t* arow, int lda, const float* B, const int32_t* brow, int ldb,
                        const int32_t* M_dev, int M_max, int I, int J, float* part, hipStream_t s);
 void launch_tn_bf16ops(const float* A, const int32_t* arow, int lda, const float* B, const int32_t* brow, int ldb,
                        const int32_t* M_dev, int M_max, int I, int J, float* part, hipStream_t s);
@@ -390,14 +386,14 @@ extern "C" dr_status dr_saved_free(dr_ctx* c, dr_saved* sv) {
 // grads[off .. off + I*J) = sum over chunks of TN partials
 static void tn_grad(dr_train* t, bool bf16, const float* A, const int32_t* arow, int lda, const float* Bm, const int32_t* brow,
                     int ldb, const int32_t* M_dev, int M_max, int I, int J, float* out, hipStream_t s) {
-  (bf16 ? launch_tn_bf16ops : launch_tn_partial)(A, arow, lda, Bm, brow, ldb, M_dev, M_max, I, J, t->part, s);
-  launch_sum_parts(t->part, tn_chunks(M_max), I * J, out, 0, s);
+  (bf16 ? launch_tn_bf16ops : launch_tn_f32)(A, arow, lda, Bm, brow, ldb, M_dev, M_max, I, J, t->part, s);
+  launch_sum_parts(t->part, tn_chunks(M_max), M_dev, TN_CHUNK, I * J, out, 0, s);
 }
 
 static void colsum_grad(dr_train* t, const float* Bm, int ldb, const int32_t* M_dev, int M_max, int J, float* out,
                         hipStream_t s) {
   launch_colsum_partial(Bm, ldb, M_dev, M_max, J, t->part, s);
-  launch_sum_parts(t->part, tn_chunks(M_max), J, out, 0, s);
+  launch_sum_parts(t->part, tn_chunks(M_max), M_dev, TN_CHUNK, J, out, 0, s);
 }
 
 // [C][48] (k = (ky*4 + kx)*3 + ch) -> [C][3][4][4]
@@ -452,7 +448,7 @@ extern "C" dr_status dr_train_backward(dr_ctx* c, dr_saved* sv, const float* dpr
   train_gemm(b16, t->dyt, nullptr, nullptr, N, 48, W(n.dec_w), t->zeros, C, EPI_STORE, t->dz, nullptr, s);
   // final LayerNorm
   launch_ln_bwd(sv->xf, nullptr, nullptr, N, C, W(n.lnfg), t->dz, t->dx, 0, 0, t->lnpart, s);
-  launch_sum_parts(t->lnpart, ln_bwd_blocks(N), 2 * C, G + po.lnfg, 0, s);  // lnf.g then lnf.b
+  launch_sum_parts(t->lnpart, ln_bwd_blocks(N), nullptr, LNB_ROWS, 2 * C, G + po.lnfg, 0, s);  // lnf.g then lnf.b
   KCHECK("decoder backward");
   for (int l = n.cfg.blocks - 1; l >= 0; --l) {
     const BlockW& b = n.blk[l];
@@ -470,7 +466,7 @@ extern "C" dr_status dr_train_backward(dr_ctx* c, dr_saved* sv, const float* dpr
     train_gemm(b16, t->dh, nullptr, sv->nq, N, R, W(b.w1T), t->zeros, C, EPI_STORE, t->dn2, nullptr, s);
     HIP_OK(c, hipMemcpyAsync(t->dx1, t->dx2, (size_t)N * C * 4, hipMemcpyDeviceToDevice, s));
     launch_ln_bwd(tb.x1, nullptr, sv->nq, N, C, W(b.ln2g), t->dn2, t->dx1, 1, 1, t->lnpart, s);
-    launch_sum_parts(t->lnpart, ln_bwd_blocks(N), 2 * C, G + pb.ln2g, 0, s);  // ln2.g then ln2.b
+    launch_sum_parts(t->lnpart, ln_bwd_blocks(N), sv->nq, LNB_ROWS, 2 * C, G + pb.ln2g, 0, s);  // ln2.g then ln2.b
     // x1 = x + Wo O + bo
     tn_grad(t, b16, t->dx1, nullptr, C, tb.o, nullptr, C, sv->nq, N, C, C, G + pb.wo, s);
     colsum_grad(t, t->dx1, C, sv->nq, N, C, G + pb.bo, s);
@@ -492,7 +488,7 @@ extern "C" dr_status dr_train_backward(dr_ctx* c, dr_saved* sv, const float* dpr
     train_gemm(b16, t->dq, nullptr, sv->nq, N, C, W(b.wqT), t->zeros, C, EPI_RESID, t->du, sv->idx, s);
     // LN1
     launch_ln_bwd(tb.x_in, nullptr, nullptr, N, C, W(b.ln1g), t->du, t->dx, 1, 0, t->lnpart, s);
-    launch_sum_parts(t->lnpart, ln_bwd_blocks(N), 2 * C, G + pb.ln1g, 0, s);  // ln1.g then ln1.b
+    launch_sum_parts(t->lnpart, ln_bwd_blocks(N), nullptr, LNB_ROWS, 2 * C, G + pb.ln1g, 0, s);  // ln1.g then ln1.b
     KCHECK("qkv backward");
   }
   // patch embedding

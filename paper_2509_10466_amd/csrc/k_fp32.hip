@@ -1,6 +1,6 @@
-// The plain FP32 path: one simple kernel per operation (LayerNorm, SIMT-tiled GEMM with a
-// bias/GELU/residual epilogue, and per-query window attention).  It is the baseline the
-// MFMA paths are measured against and the FP32 reference of the library itself.
+// Pieces of the plain FP32 path: LayerNorm rows, and per-query window attention for the
+// windows that the FP32 matrix-core attention (k_train_attn.hip) does not hold.  The linears
+// are in k_ops_gemm.hip.
 #include "dr_device.h"
 #include "dr_internal.h"
 
@@ -55,83 +55,6 @@ void launch_ln_f32(const float* x, const int32_t* rows, const int32_t* nrows_dev
   ln_kernel<float><<<(nrows_max + 3) / 4, 256, 0, s>>>(x, rows, nrows_dev, nrows_max, C, g, b, y);
 }
 
-
-// ------------------------------------------------------------------------------------------
-// SIMT GEMM: Y[m, n] = sum_k A[arow(m), k] * W[n, k] + bias[n]; 64x64 tile, BK = 16,
-// 256 threads with 4x4 outputs each.
-// ------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__ A, const int32_t* __restrict__ arows,
-                                                       const int32_t* __restrict__ m_dev, int m_max, int K,
-                                                       const float* __restrict__ W, const float* __restrict__ bias,
-                                                       int Nout, int epi, float* __restrict__ out,
-                                                       const int32_t* __restrict__ res_rows) {
-  __shared__ float As[16][64 + 4];
-  __shared__ float Ws[16][64 + 4];
-  const int M = m_dev ? m_dev[0] : m_max;
-  const int m0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
-  if (m0 >= M) return;
-  const int t = threadIdx.x;
-  const int lr = t >> 2, lk = (t & 3) * 4;  // loader: row in tile, k offset
-  const int am = m0 + lr;
-  const bool a_ok = am < M;
-  const float* arow = A + (size_t)(a_ok ? (arows ? arows[am] : am) : 0) * K;
-  const int wn = n0 + lr;
-  const bool w_ok = wn < Nout;
-  const float* wrow = W + (size_t)(w_ok ? wn : 0) * K;
-  const int ty = t >> 4, tx = t & 15;
-  float acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    float4 av = a_ok ? *reinterpret_cast<const float4*>(arow + k0 + lk) : make_float4(0, 0, 0, 0);
-    float4 wv = w_ok ? *reinterpret_cast<const float4*>(wrow + k0 + lk) : make_float4(0, 0, 0, 0);
-    As[lk + 0][lr] = av.x; As[lk + 1][lr] = av.y; As[lk + 2][lr] = av.z; As[lk + 3][lr] = av.w;
-    Ws[lk + 0][lr] = wv.x; Ws[lk + 1][lr] = wv.y; Ws[lk + 2][lr] = wv.z; Ws[lk + 3][lr] = wv.w;
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], w[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[k][ty + 16 * i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) w[j] = Ws[k][tx + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + ty + 16 * i;
-    if (m >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tx + 16 * j;
-      if (n >= Nout) continue;
-      const float y = acc[i][j] + bias[n];
-      if (epi == EPI_STORE) {
-        out[(size_t)m * Nout + n] = y;
-      } else if (epi == EPI_GELU) {
-        out[(size_t)m * Nout + n] = gelu_erf(y);
-      } else {
-        const int dst = res_rows ? res_rows[m] : m;
-        out[(size_t)dst * Nout + n] += y;
-      }
-    }
-  }
-}
-
-void launch_gemm_f32(const float* A, const int32_t* arows, const int32_t* m_dev, int m_max, int K,
-                     const float* W, const float* bias, int Nout, int epi, float* out,
-                     const int32_t* res_rows, hipStream_t s) {
-  if (m_max <= 0) return;
-  dim3 grid((m_max + 63) / 64, (Nout + 63) / 64);
-  gemm_f32_kernel<<<grid, 256, 0, s>>>(A, arows, m_dev, m_max, K, W, bias, Nout, epi, out, res_rows);
-}
 
 // ------------------------------------------------------------------------------------------
 // Window attention, FP32: one wavefront per (window, head, query).  Scores over all S keys of

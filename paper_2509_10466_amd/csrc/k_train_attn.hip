@@ -182,7 +182,7 @@ __global__ void __launch_bounds__(TA_THREADS) attn_train_fwd_kernel(int S, int C
       for (int dt = 0; dt < DH / 16; ++dt)
         *reinterpret_cast<float4*>(orow + 16 * dt + 4 * g) =
             make_float4(acc[dt][0] * inv, acc[dt][1] * inv, acc[dt][2] * inv, acc[dt][3] * inv);
-      if (g == 0) stats[(size_t)(q0 + qi) * heads + h] = make_float2(mx, sum);
+      if (stats && g == 0) stats[(size_t)(q0 + qi) * heads + h] = make_float2(mx, sum);
     }
   }
 }
