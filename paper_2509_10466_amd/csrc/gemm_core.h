@@ -55,6 +55,11 @@ __device__ __forceinline__ void vm_wait_barrier() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
+// Tells the compiler what the lgkmcnt(0) of an asm wait above did (it does not read asm), so
+// that it adds no wait of its own for the LDS reads before it.  gfx9 encoding: vmcnt 63,
+// expcnt 7, lgkmcnt 0.
+__device__ __forceinline__ void lds_reads_done() { __builtin_amdgcn_s_waitcnt(0xC07F); }
+
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 __device__ __forceinline__ void dma16(const void* gsrc, bf16_t* lds_dst) {

@@ -472,11 +472,18 @@ struct MlpCfg {
   static constexpr int NSTAGE = NKC * NHALF + NCH * PER_CHUNK;
   static constexpr int FN_C = C / 64, FN_H = HC / 64;  // 16-wide fragments per wavefront
   static constexpr int FPH = FN_C / NHALF;             // of them per C-row stage
+  static constexpr int NFW = FPH > KB1 * FN_H ? FPH : KB1 * FN_H;  // weight fragments per slice (half a stage)
+  // stage s: of W1'; else its k block and half of W_2
+  __device__ static constexpr bool is_w1(int s) {
+    return s >= NKC * NHALF && (s - NKC * NHALF) % PER_CHUNK < NW1;
+  }
+  __device__ static constexpr int kb2(int s) { return ((s - NKC * NHALF) % PER_CHUNK - NW1) / NHALF; }
+  __device__ static constexpr int half2(int s) { return ((s - NKC * NHALF) % PER_CHUNK - NW1) % NHALF; }
   // output column of wavefront wn's fragment j (lane group kg adds 4 kg): the wavefront's
   // columns are spread over the NHALF row ranges of a C-row stage, FPH fragments in each
   __device__ static constexpr int col(int wn, int j) { return (j / FPH) * CS + wn * 16 * FPH + 16 * (j % FPH); }
   static constexpr size_t RING = (size_t)ST * SLOT, ARES = (size_t)NKC * BM * 64, HRES = (size_t)NKH * BM * 64;
-  static constexpr size_t FLOATS = 2 * (size_t)C + R + 2 * WN * BM;  // b_o, b1', b_2, row sums
+  static constexpr size_t FLOATS = 2 * (size_t)C + R + 2 * WN * BM + BM;  // b_o, b1', b_2, row sums, token rows
   static constexpr size_t LDS_BYTES = (RING + ARES + HRES) * 2 + FLOATS * 4;
   static_assert(C % 64 == 0 && HC % 64 == 0 && R % HC == 0 && NKC % KB1 == 0, "shapes");
   static_assert(C % CS == 0 && FN_C % NHALF == 0 && CS % (16 * WN) == 0 && SLOT_ROWS >= HC, "C-row stages");
@@ -487,55 +494,11 @@ struct MlpCfg {
   static_assert(LDS_BYTES <= 160 * 1024, "LDS");
 };
 
-// One 64-wide k block: acc[i][j] += A[wm*TM + 16i + l16][k] W[wn*16*FN + 16j + l16][k], A and
-// W in the swizzled 64-column LDS layout.
-template <class MC, int FN, int J0 = 0, int NA = FN>
-__device__ __forceinline__ void mfma_block(const bf16* As, const bf16* Ws, f32x4_t (&acc)[MC::FM][NA]) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int wm = wv / MC::WN, wn = wv % MC::WN;
-  const int l16 = lane & 15, kg = lane >> 4;
-  bf16x8_t af[2][MC::FM], wf[2][FN];
-  static_for<2>([&](auto kk) {
-    static_for<MC::FM>([&](auto i) {
-      const int row = wm * MC::TM + 16 * i + l16;
-      af[kk][i] = *reinterpret_cast<const bf16x8_t*>(As + row * 64 + (((4 * kk + kg) ^ lds_swz(row)) * 8));
-    });
-    static_for<FN>([&](auto j) {
-      const int row = wn * 16 * FN + 16 * j + l16;
-      wf[kk][j] = *reinterpret_cast<const bf16x8_t*>(Ws + row * 64 + (((4 * kk + kg) ^ lds_swz(row)) * 8));
-    });
-  });
-  static_for<2>([&](auto kk) {
-    mfma_fence_begin();
-    static_for<MC::FM>([&](auto i) {
-      static_for<FN>([&](auto j) { acc[i][J0 + j] = mfma_bf16_16x16x32(wf[kk][j], af[kk][i], acc[i][J0 + j]); });
-    });
-    mfma_fence_end();
-  });
-}
-
-// As mfma_block with the A fragments already in registers (af[kk][i]: rows wm*TM + 16 i + l16,
-// k values 32 kk + 8 kg .. +7 of the 64-wide k block).
-template <class MC, int FN>
-__device__ __forceinline__ void mfma_block_ra(const bf16x8_t (&af)[2][MC::FM], const bf16* Ws,
-                                              f32x4_t (&acc)[MC::FM][FN]) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int wn = wv % MC::WN;
-  const int l16 = lane & 15, kg = lane >> 4;
-  bf16x8_t wf[2][FN];
-  static_for<2>([&](auto kk) {
-    static_for<FN>([&](auto j) {
-      const int row = wn * 16 * FN + 16 * j + l16;
-      wf[kk][j] = *reinterpret_cast<const bf16x8_t*>(Ws + row * 64 + (((4 * kk + kg) ^ lds_swz(row)) * 8));
-    });
-  });
-  static_for<2>([&](auto kk) {
-    mfma_fence_begin();
-    static_for<MC::FM>([&](auto i) {
-      static_for<FN>([&](auto j) { acc[i][j] = mfma_bf16_16x16x32(wf[kk][j], af[kk][i], acc[i][j]); });
-    });
-    mfma_fence_end();
-  });
+// A 16-row operand fragment (rows row0 + l % 16, k slice kk of a 64-wide k block) of a swizzled
+// 64-column LDS tile.
+__device__ __forceinline__ bf16x8_t lds_frag(const bf16* tile, int row0, int kk) {
+  const int lane = threadIdx.x & 63, row = row0 + (lane & 15), kg = lane >> 4;
+  return *reinterpret_cast<const bf16x8_t*>(tile + row * 64 + (((4 * kk + kg) ^ lds_swz(row)) * 8));
 }
 
 // Element offset of (row r, column c) in a resident [k block][BM rows][64] swizzled tile.
@@ -637,6 +600,7 @@ __global__ void __launch_bounds__(MLP_THREADS) mlp_block_kernel(const int32_t* _
   float* sb1 = sbo + C;
   float* sb2 = sb1 + R;
   float(*red)[MC::WN][MC::BM] = reinterpret_cast<float(*)[MC::WN][MC::BM]>(sb2 + C);
+  int* sdst = reinterpret_cast<int*>(sb2 + C + 2 * MC::WN * BM);
 
   const int M = m_dev[0];
   const int m0 = blockIdx.x * BM;
@@ -674,43 +638,34 @@ __global__ void __launch_bounds__(MLP_THREADS) mlp_block_kernel(const int32_t* _
     });
   // weight stages: stage s holds rows [0, stage_rows(s)) of 64 k columns; a W1' stage holds
   // KB1 blocks of HC rows, k block b of the stage at rows [b HC, (b+1) HC)
-  auto stage_rows = [](int s) {
+  constexpr auto stage_rows = [](int s) {
     if (s < MC::NKC * MC::NHALF) return MC::CS;
     const int tt = (s - MC::NKC * MC::NHALF) % MC::PER_CHUNK;
     return tt < MC::NW1 ? HC * MC::KB1 : MC::CS;
   };
-  auto issue = [&](int s) {
+  // a lane's source: a byte offset in the stage's first 64 rows (row stride C or R) from a
+  // uniform address, so a load needs no vector arithmetic and two registers serve every stage
+  const int lrow = wv * 8 + (lane >> 3), lcol = ((lane & 7) ^ lds_swz(lrow)) * 16;
+  const uint32_t off_c = lrow * C * 2 + lcol, off_r = lrow * R * 2 + lcol;
+  const int uwv = __builtin_amdgcn_readfirstlane(wv);
+  auto issue = [&](auto s) {
     const bf16* base;
-    int rows_s, ld, blk_rows;  // slot rows; source row stride; rows per k block in the slot
-    if (s < MC::NKC * MC::NHALF) {
-      const int kb = s / MC::NHALF, h = s - kb * MC::NHALF;
-      base = Wo + (size_t)h * MC::CS * C + 64 * kb;
-      rows_s = MC::CS;
-      ld = C;
-      blk_rows = MC::CS;
+    constexpr bool w2 = s >= MC::NKC * MC::NHALF && !MC::is_w1(s);
+    constexpr int ld = w2 ? R : C, blk_rows = MC::is_w1(s) ? HC : MC::CS;  // row stride; rows per k block in the slot
+    static_assert(blk_rows % (8 * NW) == 0, "whole loads of 64 rows");
+    if constexpr (s < MC::NKC * MC::NHALF) {
+      base = Wo + (size_t)(s % MC::NHALF) * MC::CS * C + 64 * (s / MC::NHALF);
     } else {
-      const int q = s - MC::NKC * MC::NHALF, j = q / MC::PER_CHUNK, tt = q - j * MC::PER_CHUNK;
-      if (tt < MC::NW1) {
+      constexpr int j = (s - MC::NKC * MC::NHALF) / MC::PER_CHUNK, tt = (s - MC::NKC * MC::NHALF) % MC::PER_CHUNK;
+      if constexpr (tt < MC::NW1)
         base = W1 + (size_t)j * HC * C + 64 * MC::KB1 * tt;
-        rows_s = HC * MC::KB1;
-        ld = C;
-        blk_rows = HC;
-      } else {
-        const int u = tt - MC::NW1, kb = u / MC::NHALF, h = u - kb * MC::NHALF;
-        base = W2 + (size_t)h * MC::CS * R + j * HC + 64 * kb;
-        rows_s = MC::CS;
-        ld = R;
-        blk_rows = MC::CS;
-      }
+      else
+        base = W2 + (size_t)MC::half2(s) * MC::CS * R + j * HC + 64 * MC::kb2(s);
     }
-    bf16* dst = ring + (s % MC::ST) * MC::SLOT;
-    static_for<MC::SLOT_ROWS / (8 * NW)>([&](auto c) {
-      const int g8 = wv + NW * c;
-      if (g8 * 8 < rows_s) {  // uniform per wavefront
-        const int row = g8 * 8 + (lane >> 3);
-        const int b = row / blk_rows, rr = row - b * blk_rows;  // blk_rows is a multiple of 8
-        dma16(base + (size_t)rr * ld + 64 * b + ((lane & 7) ^ lds_swz(row)) * 8, dst + g8 * 512);
-      }
+    bf16* dst = ring + (s % MC::ST) * MC::SLOT + uwv * 512;
+    static_for<stage_rows(s) / (8 * NW)>([&](auto c) {
+      constexpr int row = 8 * NW * c, b = row / blk_rows, rr = row % blk_rows;
+      dma16(reinterpret_cast<const char*>(base + (size_t)rr * ld + 64 * b) + (w2 ? off_r : off_c), dst + row * 64);
     });
   };
   static_for<MC::ST - 1>([&](auto s0) { issue(s0); });
@@ -731,48 +686,124 @@ __global__ void __launch_bounds__(MLP_THREADS) mlp_block_kernel(const int32_t* _
     const int i = t + MLP_THREADS * k;
     if (i < R) sb1[i] = vb1[k];
   });
+  // the token rows wait in LDS for the last epilogue (in registers they would be spilled)
+  if (wn == 0 && kg == 0) static_for<MC::FM>([&](auto i) { sdst[wm * MC::TM + 16 * i + l16] = dst[i]; });
   f32x4_t acc[MC::FM][MC::FN_C], hacc[MC::FM][MC::FN_H];
   static_for<MC::FM>([&](auto i) {
     static_for<MC::FN_C>([&](auto j) { acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; });
     static_for<MC::FN_H>([&](auto j) { hacc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; });  // set per chunk below
   });
   float mean[MC::FM], rstd[MC::FM];
-  // Before multiplying stage s: wait until it has landed (with a 3-stage ring at most the next
-  // stage's loads outstanding, or none after a stretch of other vector-memory traffic), then
-  // queue s + ST - 1.
-  bool drained = true;  // the bias loads and row indices above are vector-memory reads
-  auto enter = [&](int s) {
-    if (MC::ST == 2 || drained || s + 1 >= MC::NSTAGE)
-      vm_wait_barrier<0>();
-    else if (stage_rows(s + 1) == MC::CS)
-      vm_wait_barrier<(MC::ST == 3 ? MC::CS / (8 * NW) : 0)>();
-    else
-      vm_wait_barrier<(MC::ST == 3 ? HC * MC::KB1 / (8 * NW) : 0)>();
-    drained = false;
-    if (s + MC::ST - 1 < MC::NSTAGE) issue(s + MC::ST - 1);
-    return ring + (s % MC::ST) * MC::SLOT;
-  };
-  int s = 0;
   static_assert(MC::ST == 3, "the counted waits below assume a 3-stage ring");
-  // stage s + 1's loads per wavefront (s = 0, 1): the counts of the first two waits
-  constexpr int L1 = stage_rows(1) / (8 * NW), L2 = stage_rows(2) / (8 * NW);
-  static_for<MC::NKC * MC::NHALF>([&](auto sk) {
-    constexpr int kb = sk / MC::NHALF, h = sk % MC::NHALF;
-    const bf16* ws;
-    if constexpr (sk == 0) {  // outstanding: stage 0, stage 1, x rows
-      vm_wait_barrier<L1 + NX>();
-      drained = false;
-      issue(s + MC::ST - 1);
-      ws = ring;
-    } else if constexpr (sk == 1) {  // outstanding: stage 1, x rows, stage 2
-      vm_wait_barrier<NX + L2>();
-      issue(s + MC::ST - 1);
-      ws = ring + MC::SLOT;
-    } else {
-      ws = enter(s);
+  // Every stage is multiplied in two slices, and the fragments of slice n + 1 are read from LDS
+  // among the products of slice n, also over the stage boundary: the wait and barrier that
+  // make stage s + 1 visible come before the last products of stage s, so that the matrix
+  // cores work while the wavefronts wait and read.  (After a direct global->LDS load the
+  // compiler waits for all LDS reads before the first product that needs one, so the reads of
+  // the next slice are issued after that product, not before it.)  (Reading both slices after the barrier and
+  // then multiplying, every stage waited for all its reads: 1,100 + 360 cycles per stage for
+  // 512 of matrix-core time.)  Fragments: of W_o and W_2, slice q holds the 32-wide k slice q
+  // of the stage; of W1', KB1 of the stage's 2 KB1 (k block, slice) pairs.
+  bf16x8_t fa[2][MC::FM], fw[2][MC::NFW];
+  constexpr int S1 = MC::NKC * MC::NHALF;  // W_o stages
+  bf16x8_t ua[MC::NKC][2][MC::FM];
+  auto load_w = [&](auto s, auto q) {
+    const bf16* ws = ring + (s % MC::ST) * MC::SLOT;
+    if constexpr (MC::is_w1(s))
+      static_for<MC::KB1>([&](auto p) {
+        constexpr int pair = q * MC::KB1 + p, b = pair / 2, kk = pair % 2;
+        static_for<MC::FN_H>([&](auto j) {
+          fw[q][p * MC::FN_H + j] = lds_frag(ws + b * HC * 64, wn * 16 * MC::FN_H + 16 * j, kk);
+        });
+      });
+    else
+      static_for<MC::FPH>([&](auto j) { fw[q][j] = lds_frag(ws, wn * 16 * MC::FPH + 16 * j, q); });
+  };
+  auto load_a = [&](auto s, auto q) {  // rows of o (W_o stages) or of the H tile (W_2 stages)
+    if constexpr (!MC::is_w1(s)) {
+      const bf16* tile = s < S1 ? ares + (s / MC::NHALF) * BM * 64 : hres + MC::kb2(s) * BM * 64;
+      static_for<MC::FM>([&](auto i) { fa[q][i] = lds_frag(tile, wm * MC::TM + 16 * i, q); });
     }
-    mfma_block<MC, MC::FPH, h * MC::FPH, MC::FN_C>(ares + kb * BM * 64, ws, acc);
-    ++s;
+  };
+  // The products of slice q of stage s; `between` runs after the first of them (its operands are
+  // read again by later ones, so no register that `between` writes is still an operand of a
+  // product in flight).
+  auto multiply = [&](auto s, auto q, auto&& between) {
+    mfma_fence_begin();
+    bool first = true;
+    auto after_first = [&] {
+      if (first) {
+        first = false;
+        mfma_fence_begin();
+        between();
+        mfma_fence_begin();
+      }
+    };
+    if constexpr (MC::is_w1(s)) {
+      constexpr int tt = (s - S1) % MC::PER_CHUNK;
+      static_for<MC::KB1>([&](auto p) {
+        constexpr int pair = q * MC::KB1 + p, kb = tt * MC::KB1 + pair / 2, kk = pair % 2;
+        static_for<MC::FM>([&](auto i) {
+          static_for<MC::FN_H>([&](auto j) {
+            hacc[i][j] = mfma_bf16_16x16x32(fw[q][p * MC::FN_H + j], ua[kb][kk][i], hacc[i][j]);
+            after_first();
+          });
+        });
+      });
+    } else {
+      constexpr int j0 = (s < S1 ? s % MC::NHALF : MC::half2(s)) * MC::FPH;
+      static_for<MC::FM>([&](auto i) {
+        static_for<MC::FPH>([&](auto j) {
+          acc[i][j0 + j] = mfma_bf16_16x16x32(fw[q][j], fa[q][i], acc[i][j0 + j]);
+          after_first();
+        });
+      });
+    }
+    mfma_fence_end();
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using INX = std::integral_constant<int, NX>;
+  // Make stage s visible: wait for this wavefront's loads of it (at most the next stage's and
+  // `more` other later vector-memory loads may be outstanding), then the block barrier; every
+  // wavefront has then also finished reading stage s - 1, whose slot the loads of stage
+  // s + ST - 1 overwrite.
+  auto visible = [&](auto s, auto more) {
+    constexpr int next = s + 1 < MC::NSTAGE ? stage_rows(s + 1) / (8 * NW) : 0;
+    vm_wait_barrier<next + more>();
+    lds_reads_done();
+  };
+  // read the first slice of stage s (visible) and queue stage s + ST - 1
+  auto enter = [&](auto s, bool a_ready) {
+    load_w(s, I0{});
+    if (a_ready) load_a(s, I0{});
+    mfma_fence_begin();
+    if constexpr (s + MC::ST - 1 < MC::NSTAGE) issue(std::integral_constant<int, s + MC::ST - 1>{});
+  };
+  // Stage s with its first slice loaded; makes stage s + 1 visible before the last products.
+  auto stage = [&](auto s, auto more, bool enter_next, bool a_ready) {
+    constexpr bool last = s + 1 >= MC::NSTAGE;
+    using Next = std::integral_constant<int, last ? s : s + 1>;
+    multiply(s, I0{}, [&] {
+      load_w(s, I1{});
+      load_a(s, I1{});
+    });
+    if constexpr (!last)
+      if (enter_next) visible(Next{}, more);
+    multiply(s, I1{}, [&] {
+      if constexpr (!last)
+        if (enter_next) enter(Next{}, a_ready);
+    });
+  };
+  // The x rows were requested after stages 0 and 1, so the first two waits leave them
+  // outstanding and the third covers them.
+  visible(I0{}, INX{});
+  enter(I0{}, true);
+  static_for<S1>([&](auto s) {
+    if constexpr (s == 0)
+      stage(s, INX{}, S1 > 1, true);
+    else
+      stage(s, I0{}, s + 1 < S1, true);
   });
   // x1 = x + o W_o^T + b_o; u2 = normalise(x1) into the resident tile (every wavefront has
   // finished reading o there: resid_rows passes two block barriers)
@@ -794,33 +825,28 @@ __global__ void __launch_bounds__(MLP_THREADS) mlp_block_kernel(const int32_t* _
       acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     });
   });
-  drained = true;  // x was read and written
   // this wavefront's u2 fragments stay in registers for every hidden chunk
   lds_barrier();
-  bf16x8_t ua[MC::NKC][2][MC::FM];
   static_for<MC::NKC>([&](auto kb) {
     static_for<2>([&](auto kk) {
-      static_for<MC::FM>([&](auto i) {
-        const int row = wm * MC::TM + 16 * i + l16;
-        ua[kb][kk][i] = *reinterpret_cast<const bf16x8_t*>(ares + kb * BM * 64 + row * 64 +
-                                                           (((4 * kk + kg) ^ lds_swz(row)) * 8));
-      });
+      static_for<MC::FM>([&](auto i) { ua[kb][kk][i] = lds_frag(ares + kb * BM * 64, wm * MC::TM + 16 * i, kk); });
     });
   });
+  // x was read (and written): wait for everything, the ring's two stages included
+  vm_wait_barrier<0>();
+  lds_reads_done();
+  enter(std::integral_constant<int, S1>{}, true);
   // unrolled: every stage index, ring slot and wait count below is a constant (1.2 % per clip
   // at 5 x 240 x 432, timed back to back on one GPU)
-#pragma unroll
-  for (int j = 0; j < MC::NCH; ++j) {
+  static_for<MC::NCH>([&](auto j) {
     // the chunk's accumulators start at its bias b1' (the GELU epilogue then adds nothing)
     static_for<MC::FN_H>([&](auto jj) {
-      const float4 b4 = *reinterpret_cast<const float4*>(sb1 + j * HC + wn * 16 * MC::FN_H + 16 * jj + 4 * kg);
-      static_for<MC::FM>([&](auto i) { hacc[i][jj] = f32x4_t{b4.x, b4.y, b4.z, b4.w}; });
+      const bf16x8_t b4 = *reinterpret_cast<const bf16x8_t*>(sb1 + j * HC + wn * 16 * MC::FN_H + 16 * jj + 4 * kg);
+      static_for<MC::FM>([&](auto i) { hacc[i][jj] = __builtin_bit_cast(f32x4_t, b4); });
     });
-    static_for<MC::NW1>([&](auto tt) {
-      const bf16* ws = enter(s);
-      static_for<MC::KB1>([&](auto b) { mfma_block_ra<MC, MC::FN_H>(ua[tt * MC::KB1 + b], ws + b * HC * 64, hacc); });
-      ++s;
-    });
+    constexpr int s1 = S1 + j * MC::PER_CHUNK, s2 = s1 + MC::NW1;
+    // (the last W1' stage enters the first W_2 stage, whose H rows do not exist yet)
+    static_for<MC::NW1>([&](auto tt) { stage(std::integral_constant<int, s1 + tt>{}, I0{}, true, tt + 1 < MC::NW1); });
     // hidden chunk j: GELU into the H tile (its previous contents were consumed before this
     // stage's barrier); the weights carry GELU's constant factors (gelu_scaled)
     static_for<MC::FM>([&](auto i) {
@@ -828,20 +854,16 @@ __global__ void __launch_bounds__(MLP_THREADS) mlp_block_kernel(const int32_t* _
       static_for<MC::FN_H>([&](auto jj) {
         const int c = wn * 16 * MC::FN_H + 16 * jj + 4 * kg;
         const f32x4_t& a = hacc[i][jj];
-        uint2 pk;
-        pk.x = pack_bf2(gelu_scaled(a[0]), gelu_scaled(a[1]));
-        pk.y = pack_bf2(gelu_scaled(a[2]), gelu_scaled(a[3]));
-        *reinterpret_cast<uint2*>(hres + res_off<MC::BM>(r, c)) = pk;
+        *reinterpret_cast<bf16x4_t*>(hres + res_off<MC::BM>(r, c)) =
+            bf16x4_t{(__bf16)gelu_scaled(a[0]), (__bf16)gelu_scaled(a[1]), (__bf16)gelu_scaled(a[2]), (__bf16)gelu_scaled(a[3])};
       });
     });
-    static_for<MC::NKH * MC::NHALF>([&](auto sk) {
-      constexpr int kb = sk / MC::NHALF, h = sk % MC::NHALF;
-      const bf16* ws = enter(s);
-      mfma_block<MC, MC::FPH, h * MC::FPH, MC::FN_C>(hres + kb * BM * 64, ws, acc);
-      ++s;
-    });
-  }
+    lds_barrier();
+    load_a(std::integral_constant<int, s2>{}, I0{});
+    static_for<MC::NKH * MC::NHALF>([&](auto u) { stage(std::integral_constant<int, s2 + u>{}, I0{}, true, true); });
+  });
   // x2 = x1 + h W_2^T + b_2; x^ = normalise(x2)
+  static_for<MC::FM>([&](auto i) { dst[i] = sdst[wm * MC::TM + 16 * i + l16]; });
   if constexpr (!MC::X1_REGS) load_resid<MC>(x, dst, xo);  // this thread's own stores, an L2 hit
   resid_rows<MC>(acc, sb2, x, dst, xo, red, mean, rstd);
   static_for<MC::FM>([&](auto i) {
