@@ -331,8 +331,9 @@ constexpr int ROW_TILE = 64;
 // counts ntiles[2])
 void launch_window_order(const Geo& g, const int32_t* wcount, const uint8_t* flag, int32_t* order, int32_t* tiles,
                          int32_t* ntiles, hipStream_t s);
-void launch_qkv_stream(const Geo& g, int C, int heads, const bf16* xh, const uint8_t* flag, const bf16* w,
-                       const float* bias, bf16* q, const StreamTable& tab, hipStream_t s);
+// stream mode: Q of the listed tiles with a flagged token, K/V of every token
+void launch_qkv_stream(const Geo& g, int C, int heads, const bf16* xh, const int32_t* tiles, const int32_t* ntiles,
+                       const bf16* w, const float* bias, bf16* q, const StreamTable& tab, hipStream_t s);
 void launch_fc1_bf16(int m_max, const int32_t* m_dev, int C, int R, const bf16* u2, const bf16* w,
                      const float* bias, bf16* h, hipStream_t s);
 bool resid_ln_supported(int C);

@@ -198,7 +198,7 @@ static dr_status stream_step_locked(dr_ctx* c, Work& w, int n, const int32_t* si
     tab.slot_stride = (long long)L * blk_elems;
     tab.vslot_stride = (long long)L * vblk_elems;
     tab.sfp = ring_vt_frame_stride(g.S);
-    LAUNCH(ST_QKV, launch_qkv_stream(g, C, net.cfg.heads, w.xh, w.flag, b.wqkvf16, b.bqkvf, w.q16, tab, s));
+    LAUNCH(ST_QKV, launch_qkv_stream(g, C, net.cfg.heads, w.xh, w.tiles, w.ntiles, b.wqkvf16, b.bqkvf, w.q16, tab, s));
     if (!decoupled) {
       LAUNCH(ST_ATTN, launch_attn_ring(tab, g, C, net.cfg.heads, net.cfg.win_t, w.q16, w.idx, w.woff, w.worder, w.o16, s));
     } else if (l % 2 == 0) {

@@ -77,6 +77,7 @@ struct GemmTile {
   static constexpr int STAGE = ROWS * 64;           // bf16 elements per stage
   static constexpr size_t LDS_BYTES = (size_t)ST * STAGE * 2;
   static_assert(NW == 4 || NW == 8, "4 or 8 wavefronts");
+  static_assert(BM % 32 == 0 && BN % 32 == 0, "whole 32-row groups of each operand");
   static_assert(TM % 16 == 0 && TN % 16 == 0 && BM % 16 == 0, "fragment multiples");
   static_assert(ROWS % (8 * NW) == 0, "whole loads");
   static_assert(ST >= 2 && (ST - 2) * LOADS < 64, "vmcnt range");
@@ -86,12 +87,16 @@ struct GemmTile {
 // caller), W: [*][K] rows n0 .. n0+BN-1; K a multiple of 64, M >= 1.  `lds` holds
 // GemmTile::LDS_BYTES.  On return every wavefront has finished reading LDS only after the
 // caller's next barrier.
-// KC > 0: K = KC known at compile time (the k loop unrolled, its waits fixed); else K at run time.
-template <class TL, int KC = 0>
+//
+// A stage is multiplied in two 32-wide slices, and the fragments of the next slice are read
+// from LDS right after the first product of the current one, also over the stage boundary:
+// the wait and barrier that make stage kt + 1 visible come before the last products of stage
+// kt.  (After a direct global->LDS load the compiler waits for every LDS read before the first
+// product that needs one, so reads issued before the products would not overlap with them.)
+template <class TL>
 __device__ __forceinline__ void gemm_core(const bf16_t* __restrict__ A, int M, int m0,
-                                          const bf16_t* __restrict__ W, int n0, int K_, bf16_t* lds,
+                                          const bf16_t* __restrict__ W, int n0, int K, bf16_t* lds,
                                           f32x4_t (&acc)[TL::FM][TL::FN]) {
-  const int K = KC ? KC : K_;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int wm = wv / TL::WN, wn = wv % TL::WN;
   const int l16 = lane & 15, kg = lane >> 4;
@@ -106,60 +111,86 @@ __device__ __forceinline__ void gemm_core(const bf16_t* __restrict__ A, int M, i
     const int row = (wv + TL::NW * c) * 8 + (lane >> 3);
     const int chunk = (lane & 7) ^ lds_swz(row);
     const bf16_t* base;
-    if (row < TL::BM) {
-      const int m = min(m0 + row, M - 1);
-      base = A + (size_t)m * K;
-    } else {
+    if (row < TL::BM)
+      base = A + (size_t)min(m0 + row, M - 1) * K;
+    else
       base = W + (size_t)(n0 + row - TL::BM) * K;
-    }
     src[c] = base + chunk * 8;
   });
   auto issue = [&](int kt, int buf) {
     bf16_t* dst = lds + buf * TL::STAGE;
     static_for<TL::LOADS>([&](auto c) { dma16(src[c] + kt * 64, dst + (wv + TL::NW * c) * 512); });
   };
-  // per-lane LDS element offsets of the operand rows (chunk position applied per k slice)
-  int arow[TL::FM], wrow[TL::FN];
-  static_for<TL::FM>([&](auto i) { arow[i] = wm * TL::TM + 16 * i + l16; });
-  static_for<TL::FN>([&](auto j) { wrow[j] = TL::BM + wn * TL::TN + 16 * j + l16; });
-
+  bf16x8_t af[2][TL::FM], wf[2][TL::FN];
+  auto read = [&](int kt, auto kk) {  // the fragments of slice kk of stage kt
+    const bf16_t* sb = lds + (kt % TL::ST) * TL::STAGE;
+    static_for<TL::FM>([&](auto i) {
+      const int r = wm * TL::TM + 16 * i + l16;
+      af[kk][i] = *reinterpret_cast<const bf16x8_t*>(sb + r * 64 + ((4 * kk + kg) ^ lds_swz(r)) * 8);
+    });
+    static_for<TL::FN>([&](auto j) {
+      const int r = TL::BM + wn * TL::TN + 16 * j + l16;
+      wf[kk][j] = *reinterpret_cast<const bf16x8_t*>(sb + r * 64 + ((4 * kk + kg) ^ lds_swz(r)) * 8);
+    });
+  };
+  // the products of slice kk; `between` runs after the first of them
+  auto multiply = [&](auto kk, auto&& between) {
+    mfma_fence_begin();
+    bool first = true;
+    static_for<TL::FM>([&](auto i) {
+      static_for<TL::FN>([&](auto j) {
+        acc[i][j] = mfma_bf16_16x16x32(wf[kk][j], af[kk][i], acc[i][j]);
+        if (first) {
+          first = false;
+          mfma_fence_begin();
+          between();
+          mfma_fence_begin();
+        }
+      });
+    });
+    mfma_fence_end();
+    // the first product's operands stay allocated: nothing written in `between` may share
+    // their registers while it is in flight
+    asm volatile("" ::"v"(wf[kk][0]), "v"(af[kk][0]));
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
   const int nk = K / 64;
-  static_for<TL::ST - 1>([&](auto s) {
-    if (s < nk) issue(s, s);
-  });
-  auto stage = [&](int kt) {
-    const int ahead = min(TL::ST - 2, nk - 1 - kt);  // later stages already in flight
+  // stage kt landed (the later stages already queued may be outstanding) and, behind the
+  // barrier, stage kt - 1 read by every wavefront
+  auto visible = [&](int kt) {
+    const int ahead = min(TL::ST - 2, nk - 1 - kt);
     static_for<TL::ST - 1>([&](auto a) {
       if (a == ahead) vm_wait_barrier<a * TL::LOADS>();
     });
+    lds_reads_done();
+  };
+  auto enter = [&](int kt) {
+    read(kt, I0{});
+    mfma_fence_begin();
     if (kt + TL::ST - 1 < nk) issue(kt + TL::ST - 1, (kt + TL::ST - 1) % TL::ST);
-    const bf16_t* sb = lds + (kt % TL::ST) * TL::STAGE;
-    // both 32-wide k slices of the stage are read before the first MFMA group, so the
-    // second slice's LDS latency hides behind the first group
-    bf16x8_t af[2][TL::FM], wf[2][TL::FN];
-    static_for<2>([&](auto kk) {
-      static_for<TL::FM>([&](auto i) {
-        const int c = (4 * kk + kg) ^ lds_swz(arow[i]);
-        af[kk][i] = *reinterpret_cast<const bf16x8_t*>(sb + arow[i] * 64 + c * 8);
-      });
-      static_for<TL::FN>([&](auto j) {
-        const int c = (4 * kk + kg) ^ lds_swz(wrow[j]);
-        wf[kk][j] = *reinterpret_cast<const bf16x8_t*>(sb + wrow[j] * 64 + c * 8);
-      });
-    });
-    static_for<2>([&](auto kk) {
-      mfma_fence_begin();
-      static_for<TL::FM>([&](auto i) {
-        static_for<TL::FN>([&](auto j) { acc[i][j] = mfma_bf16_16x16x32(wf[kk][j], af[kk][i], acc[i][j]); });
-      });
-      mfma_fence_end();
+  };
+  auto stage = [&](int kt) {
+    multiply(I0{}, [&] { read(kt, I1{}); });
+    const bool more = kt + 1 < nk;
+    if (more) visible(kt + 1);
+    multiply(I1{}, [&] {
+      if (more) enter(kt + 1);
     });
   };
-  if constexpr (KC > 0)
-    static_for<KC / 64>([&](auto kt) { stage(kt); });
-  else
-    for (int kt = 0; kt < nk; ++kt) stage(kt);
+  static_for<TL::ST - 1>([&](auto s) {
+    if (s < nk) issue(s, s);
+  });
+  visible(0);
+  enter(0);
+  for (int kt = 0; kt < nk; ++kt) stage(kt);
 }
+
+// A lane's results of fragments 2p and 2p + 1 become 8 consecutive channels of its token (16-byte
+// stores along a row) if W's fragment f takes row lane8_row(f, r) for lane row r, instead of
+// 16 f + r.  These rows are 4 and 4 apart, so they are swizzled by lane8_swz, not by row & 7.
+__device__ __forceinline__ int lane8_row(int f, int r) { return 32 * (f >> 1) + 8 * (r >> 2) + 4 * (f & 1) + (r & 3); }
+__device__ __forceinline__ int lane8_swz(int row) { return (row & 3) | ((row >> 1) & 4); }
 
 // Tile order: consecutive workgroups are dispatched round-robin over the 8 XCDs (each with
 // its own L2).  Workgroup b runs on XCD b % 8; it is given row tile (k / nt) * 8 + b % 8 and

@@ -59,22 +59,8 @@ struct QkvRow {
   int part;    // 0 Q, 1 K, 2 V
 };
 
-__device__ __forceinline__ void qkv_store(const QkvRow& r, int c, int C, int dsh, int kstride, int vstride,
-                                          const float4& b4, const f32x4_t& a) {
-  const float y0 = a[0] + b4.x, y1 = a[1] + b4.y, y2 = a[2] + b4.z, y3 = a[3] + b4.w;
-  if (r.part == 2) {
-    bf16* dst = r.base + (size_t)c * vstride;
-    dst[0] = f2bf(y0);
-    dst[vstride] = f2bf(y1);
-    dst[2 * vstride] = f2bf(y2);
-    dst[3 * vstride] = f2bf(y3);
-    return;
-  }
-  const int off = r.part == 0 ? c : (c >> dsh) * kstride + (c & ((1 << dsh) - 1));
-  uint2 pk;
-  pk.x = pack_bf2(y0, y1);
-  pk.y = pack_bf2(y2, y3);
-  *reinterpret_cast<uint2*>(r.base + off) = pk;
+__device__ __forceinline__ u32x4_t pack_bf8(const f32x4_t& a, const f32x4_t& b) {
+  return u32x4_t{pack_bf2(a[0], a[1]), pack_bf2(a[2], a[3]), pack_bf2(b[0], b[1]), pack_bf2(b[2], b[3])};
 }
 
 struct QkvOut {
@@ -88,11 +74,8 @@ struct QkvOut {
     if (part == 1) return {k + (((size_t)w * heads * Spad + s) << dsh), 1};
     return {vt + (((size_t)w * heads) << dsh) * spv + s, 2};
   }
-  // the bias of channels n .. n + 3, and the store of a fragment of row r with it
-  __device__ __forceinline__ float4 bias4(int n) const { return *reinterpret_cast<const float4*>(bias + n); }
-  __device__ __forceinline__ void store_b(const QkvRow& r, int n, const float4& b4, const f32x4_t& a) const {
-    qkv_store(r, n - r.part * C, C, dsh, Spad << dsh, spv, b4, a);
-  }
+  __device__ __forceinline__ int kstride() const { return Spad << dsh; }  // between heads of K
+  __device__ __forceinline__ int vstride() const { return spv; }          // between channels of V^T
 };
 
 // Stream mode: Q rows into the batch buffer; K [win_f][head][S_f][dh] and V^T
@@ -111,126 +94,252 @@ struct StreamQkvOut {
     if (part == 1) return {pick(tab.k, r) + slot * tab.slot_stride + (((size_t)wl * heads * Sf + s) << dsh), 1};
     return {pick(tab.v, r) + slot * tab.vslot_stride + (((size_t)wl * heads) << dsh) * tab.sfp + s, 2};
   }
-  __device__ __forceinline__ float4 bias4(int n) const { return *reinterpret_cast<const float4*>(bias + n); }
-  __device__ __forceinline__ void store_b(const QkvRow& r, int n, const float4& b4, const f32x4_t& a) const {
-    qkv_store(r, n - r.part * C, C, dsh, Sf << dsh, tab.sfp, b4, a);
-  }
+  __device__ __forceinline__ int kstride() const { return Sf << dsh; }
+  __device__ __forceinline__ int vstride() const { return tab.sfp; }
 };
 
-// One Q/K/V tile (rows m0 .., columns n0 ..).  Row-then-column epilogue: out.row(m, n0)
-// computes the destination of token m once (the column tile's part of the output is uniform
-// over the tile) and out.store_b(row, n, b4, a) adds the fragment's channel offset, which
-// keeps per-token address arithmetic (divisions, table selects) out of the per-fragment
-// path.  The row destinations and this lane's bias values are fetched before the product, so
-// that their latency hides behind it.
-template <class TL, class Out, int KC = 0>
-__device__ __forceinline__ void qkv_tile(int M, int m0, int n0, int C, const bf16* __restrict__ xh,
-                                         const bf16* __restrict__ W, bf16* ring, const Out& out) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+// Q/K/V tiles.  Clip mode runs only the row tiles listed with the window order (Q tiles
+// holding a flagged token; K/V tiles touching a window with queries -- keys and values of a
+// window without queries are never read); stream mode keeps K/V of every token (kv_all: later
+// frames may query any window) and lists only the Q tiles.  A block tile is one or two listed
+// row tiles (BM / ROW_TILE) by BN columns of one part.  Tiles are numbered Q column tiles
+// first, then K/V (each part XCD-ordered as xcd_tile); block b runs tiles b, b + gridDim, ...
+// (gridDim a multiple of 8, so they stay on its XCD).
+//
+// A block's tiles form one stream of 64-wide k stages through a 2-stage ring: the first two
+// stages of the next tile are queued before this tile's epilogue, so that neither their
+// latency nor the block start shows (one block per tile: 18,000 cycles at K = 384 for 6,100 of
+// products, with 128 x 128 tiles two per CU).  Slices and barriers as in gemm_core.
+// W's fragments follow lane8_row, so a lane's results are 8 consecutive channels of a token:
+// Q and K rows are written 16 bytes per lane (8 bytes per lane: 19.2 us instead of 17.7 us at
+// 32,400 rows of 256); V^T rows hold tokens and are written 2 bytes per lane, 16 lanes side by
+// side (16 bytes of 8 tokens per lane measured slower wherever a run crosses a window: 17.7 ->
+// 21.2 us at 225-token windows, 11.1 -> 16.9 us at 45).
+template <class TL, class Out, int C>
+__global__ void __launch_bounds__(TL::THREADS, TL::BM == ROW_TILE ? 6 : 2) qkv_kernel(int M, const bf16* __restrict__ xh,
+                                                          const int32_t* __restrict__ tiles,
+                                                          const int32_t* __restrict__ ntiles, int kv_all,
+                                                          const bf16* __restrict__ W, Out out) {
+  constexpr int SUB = TL::BM / ROW_TILE, NA = TL::BM / (8 * TL::NW), NB = TL::BN / (8 * TL::NW);
+  constexpr bool ONE = SUB == 1;  // one tile per block (the grid covers them all)
+  static_assert(SUB * ROW_TILE == TL::BM && SUB <= 2 && TL::ST == 2, "listed row tiles, 2-stage ring");
+  static_assert(TL::BM % (8 * TL::NW) == 0 && TL::BN % (8 * TL::NW) == 0 && TL::FN % 2 == 0, "whole loads, fragment pairs");
+  static_assert(C % TL::BN == 0 && (C == 64 || C % 128 == 0), "whole column tiles; the ring half of a stage is fixed");
+  extern __shared__ __align__(16) bf16 ring[];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wv / TL::WN, wn = wv % TL::WN, l16 = lane & 15, kg = lane >> 4;
-  QkvRow rr[TL::FM];
-  static_for<TL::FM>([&](auto f) { rr[f] = out.row(min(m0 + wm * TL::TM + 16 * f + l16, M - 1), n0); });
-  float4 b4[TL::FN];
-  static_for<TL::FN>([&](auto j) { b4[j] = out.bias4(n0 + wn * TL::TN + 16 * j + 4 * kg); });
-  f32x4_t acc[TL::FM][TL::FN];
-  gemm_core<TL, KC>(xh, M, m0, W, n0, C, ring, acc);
-  static_for<TL::FM>([&](auto f) {
-    if (m0 + wm * TL::TM + 16 * f + l16 < M)
-      static_for<TL::FN>([&](auto j) { out.store_b(rr[f], n0 + wn * TL::TN + 16 * j + 4 * kg, b4[j], acc[f][j]); });
-  });
-}
+  const int mt = (M + ROW_TILE - 1) / ROW_TILE;
+  const int nq = ntiles[0], nkv = kv_all ? mt : ntiles[1];
+  const int ntq = C / TL::BN, gq = xcd_grid((nq + SUB - 1) / SUB, ntq);
+  const int total = gq + xcd_grid((nkv + SUB - 1) / SUB, 2 * ntq);
 
-// Tile skipping: a Q column tile runs only for row tiles holding a flagged token; a K/V
-// column tile only for row tiles touching a window with queries (clip mode) -- keys and
-// values of a window without queries are never read.  Stream mode keeps K/V of every token
-// (later frames may query any window): wcount == nullptr.
-template <class TL, class Out>
-__global__ void __launch_bounds__(TL::THREADS) qkv_kernel(int M, int C, int S, const bf16* __restrict__ xh,
-                                                  const uint8_t* __restrict__ flag,
-                                                  const int32_t* __restrict__ wcount,
-                                                  const bf16* __restrict__ W, Out out) {
-  extern __shared__ __align__(16) bf16 ring[];
-  const int mt = (M + TL::BM - 1) / TL::BM, nt = 3 * C / TL::BN;
-  int rt, ct;
-  xcd_tile(blockIdx.x, nt, rt, ct);
-  if (rt >= mt) return;
-  const int m0 = rt * TL::BM, n0 = ct * TL::BN;
-  const bool is_q = n0 < C;
-  int need = 0;
-  if (threadIdx.x < TL::BM && m0 + (int)threadIdx.x < M) {
-    const int m = m0 + threadIdx.x;
-    need = is_q ? flag[m] != 0 : (wcount ? wcount[m / S] > 0 : 1);
-  }
-  if (!__syncthreads_or(need)) return;
-  qkv_tile<TL>(M, m0, n0, C, xh, W, ring, out);
-}
-
-// Clip mode: blocks run only the listed row tiles (computed with the window order).  Block b
-// takes, in dispatch order, the Q column tiles of the tiles holding a flagged token, then the
-// K/V column tiles of the tiles touching a window with queries (each part XCD-ordered as
-// xcd_tile), and the slots past both lists exit, last.
-template <class TL, class Out, int KC>
-__global__ void __launch_bounds__(TL::THREADS) qkv_list_kernel(int M, int C_, const bf16* __restrict__ xh,
-                                                       const int32_t* __restrict__ tiles,
-                                                       const int32_t* __restrict__ ntiles, const bf16* __restrict__ W,
-                                                       Out out) {
-  static_assert(TL::BM == ROW_TILE, "row tiles are listed in ROW_TILE units");
-  static_assert(KC % TL::BN == 0, "whole column tiles");
-  const int C = KC ? KC : C_;
-  extern __shared__ __align__(16) bf16 ring[];
-  const int mt = (M + TL::BM - 1) / TL::BM;
-  const int ntq = C / TL::BN, gq = xcd_grid(ntiles[0], ntq);
-  const bool is_q = (int)blockIdx.x < gq;
-  const int b = is_q ? blockIdx.x : blockIdx.x - gq;
-  int i, ct;
-  xcd_tile(b, is_q ? ntq : 2 * ntq, i, ct);
-  if (i >= ntiles[is_q ? 0 : 1]) return;
-  const int m0 = tiles[(is_q ? 0 : mt) + i] * TL::BM, n0 = (is_q ? 0 : C) + ct * TL::BN;
-  qkv_tile<TL, Out, KC>(M, m0, n0, C, xh, W, ring, out);
-}
-
-template <class TL, int KC, class Out>
-static void qkv_list_launch(int M, int C, const bf16* xh, const int32_t* tiles, const int32_t* ntiles, const bf16* w,
-                            const Out& out, hipStream_t s) {
-  static bool attr = false;
-  if (!attr) {
-    allow_lds(qkv_list_kernel<TL, Out, KC>, TL::LDS_BYTES);
-    attr = true;
-  }
-  const int mt = (M + TL::BM - 1) / TL::BM;
-  const int grid = xcd_grid(mt, C / TL::BN) + xcd_grid(mt, 2 * C / TL::BN);
-  qkv_list_kernel<TL, Out, KC><<<grid, TL::THREADS, TL::LDS_BYTES, s>>>(M, C, xh, tiles, ntiles, w, out);
-}
-
-// The network widths get their own instantiation, with the k loop unrolled (0.8 % per clip at
-// 5 x 240 x 432 and 5 x 720 x 1280, timed back to back on one GPU); other widths take K at
-// run time.
-template <class TL, class Out>
-static void qkv_list_by_c(int M, int C, const bf16* xh, const int32_t* tiles, const int32_t* ntiles, const bf16* w,
-                          const Out& out, hipStream_t s) {
-  if constexpr (TL::BN == 128) {
-    switch (C) {
-      case 128: return qkv_list_launch<TL, 128>(M, C, xh, tiles, ntiles, w, out, s);
-      case 256: return qkv_list_launch<TL, 256>(M, C, xh, tiles, ntiles, w, out, s);
-      case 384: return qkv_list_launch<TL, 384>(M, C, xh, tiles, ntiles, w, out, s);
-      default: break;
+  // the tile: tokens m0 .. and m1 .. (m1 = M: none), columns n0 ..
+  struct Tile {
+    int slot, m0, m1, n0;
+  };
+  auto find = [&](int slot) {  // the first slot from `slot` on that holds a tile, or total
+    Tile t{total, 0, 0, 0};
+    for (; slot < total; slot += gridDim.x) {
+      const bool is_q = slot < gq;
+      const int nt = is_q ? ntq : 2 * ntq;
+      int i, ct;
+      xcd_tile(is_q ? slot : slot - gq, nt, i, ct);
+      // the column tiles of a row are rotated by about one per round of the grid, so that a
+      // block's tiles are not all V tiles, whose epilogue is the longest (without it 173 us
+      // instead of 93 us at 129,600 rows of 256)
+      if (!ONE) ct = (ct + (i >> 3) * nt / (int)(gridDim.x >> 3)) % nt;
+      const int n = is_q ? nq : nkv, first = i * SUB;
+      if (first >= n) {
+        if (ONE) break;
+        continue;
+      }
+      const bool two = SUB == 2 && first + 1 < n;
+      const int32_t* list = tiles + (is_q ? 0 : mt) + first;
+      const bool listed = is_q || !kv_all;
+      t = {slot, (listed ? list[0] : first) * ROW_TILE, two ? (listed ? list[1] : first + 1) * ROW_TILE : M,
+           (is_q ? 0 : C) + ct * TL::BN};
+      break;
     }
-  } else if (C == 64) {
-    return qkv_list_launch<TL, 64>(M, C, xh, tiles, ntiles, w, out, s);
+    return t;
+  };
+  auto token = [&](const Tile& t, int r) {  // token of tile row r, or one >= M
+    return SUB == 1 || r < ROW_TILE ? t.m0 + r : t.m1 + r - ROW_TILE;
+  };
+  // a lane's sources, as byte offsets from uniform addresses
+  const int lrow = wv * 8 + (lane >> 3);
+  const uint32_t woff = lrow * C * 2 + ((lane & 7) ^ lane8_swz(lrow)) * 16;
+  static_assert((8 * TL::NW) % 16 == 0, "lane8_swz repeats every 16 rows");
+  uint32_t aoff[NA];
+  const char *abase[SUB], *wbase;
+  auto aim = [&](const Tile& t) {
+    static_for<NA>([&](auto c) {
+      constexpr int first = 8 * TL::NW * c;  // the tile row of lrow 0
+      const int m0 = first < ROW_TILE ? t.m0 : t.m1, row = first % ROW_TILE + lrow;
+      aoff[c] = min(row, max(M - 1 - m0, 0)) * C * 2 + ((lane & 7) ^ lds_swz(row)) * 16;
+    });
+    abase[0] = reinterpret_cast<const char*>(xh + (size_t)t.m0 * C);
+    if constexpr (SUB == 2) abase[1] = reinterpret_cast<const char*>(xh + (size_t)(t.m1 < M ? t.m1 : 0) * C);
+    wbase = reinterpret_cast<const char*>(W + (size_t)t.n0 * C);
+  };
+  auto issue = [&](int kt, int buf) {
+    bf16* dst = ring + buf * TL::STAGE + wv * 512;
+    static_for<NA>([&](auto c) {
+      dma16(abase[8 * TL::NW * c / ROW_TILE] + kt * 128 + aoff[c], dst + 8 * TL::NW * c * 64);
+    });
+    static_for<NB>([&](auto c) {
+      dma16(wbase + ((size_t)8 * TL::NW * c * C + kt * 64) * 2 + woff, dst + (TL::BM + 8 * TL::NW * c) * 64);
+    });
+  };
+  bf16x8_t af[2][TL::FM], wf[2][TL::FN];
+  auto read = [&](int buf, auto kk) {
+    const bf16* sb = ring + buf * TL::STAGE;
+    static_for<TL::FM>([&](auto i) {
+      const int r = wm * TL::TM + 16 * i + l16;
+      af[kk][i] = *reinterpret_cast<const bf16x8_t*>(sb + r * 64 + ((4 * kk + kg) ^ lds_swz(r)) * 8);
+    });
+    static_for<TL::FN>([&](auto j) {
+      const int r = wn * TL::TN + lane8_row(j, l16);
+      wf[kk][j] = *reinterpret_cast<const bf16x8_t*>(sb + (TL::BM + r) * 64 + ((4 * kk + kg) ^ lane8_swz(r)) * 8);
+    });
+  };
+  f32x4_t acc[TL::FM][TL::FN];
+  auto multiply = [&](auto kk, auto&& between) {
+    mfma_fence_begin();
+    bool first = true;
+    static_for<TL::FM>([&](auto i) {
+      static_for<TL::FN>([&](auto j) {
+        acc[i][j] = mfma_bf16_16x16x32(wf[kk][j], af[kk][i], acc[i][j]);
+        if (first) {
+          first = false;
+          mfma_fence_begin();
+          between();
+          mfma_fence_begin();
+        }
+      });
+    });
+    mfma_fence_end();
+    asm volatile("" ::"v"(wf[kk][0]), "v"(af[kk][0]));  // not reallocated while in flight
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+
+  constexpr int nk = C / 64;
+  Tile t = find(blockIdx.x);
+  if (t.slot >= total) return;
+  aim(t);
+  issue(0, 0);
+  vm_wait_barrier<0>();
+  lds_reads_done();
+  read(0, I0{});
+  mfma_fence_begin();
+  if (nk > 1) issue(1, 1);
+  int buf = 0;  // ring half of the stage being multiplied
+  for (;;) {
+    const Tile nx = ONE ? Tile{total, 0, 0, 0} : find(t.slot + gridDim.x);
+    const bool last = ONE || nx.slot >= total;
+    if (nk == 1 && !last) {  // the next tile's only stage (this tile's is in registers next)
+      aim(nx);
+      issue(0, buf ^ 1);
+    }
+    const int part = t.n0 / C, c0 = t.n0 - part * C + wn * TL::TN + 8 * kg;
+    f32x4_t bv[TL::FN];
+    static_for<TL::FN>([&](auto j) {
+      bv[j] = *reinterpret_cast<const f32x4_t*>(out.bias + part * C + c0 + 32 * (j / 2) + 4 * (j % 2));
+    });
+    static_for<TL::FM>([&](auto i) {
+      static_for<TL::FN>([&](auto j) { acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; });
+    });
+    // Stage kt with its first slice read.  The stage two further on is queued once every
+    // wavefront has read this one: stage kt + 2 of this tile, or of the next tile.
+    auto stage = [&](int kt) {
+      const bool more = kt + 1 < nk || !last;
+      multiply(I0{}, [&] { read(buf, I1{}); });
+      if (more) {
+        vm_wait_barrier<0>();
+        lds_reads_done();
+      }
+      multiply(I1{}, [&] {
+        if (more) {
+          read(buf ^ 1, I0{});
+          mfma_fence_begin();
+          if (kt + 2 < nk) {
+            issue(kt + 2, buf);
+          } else if (!last && nk > 1) {
+            if (kt + 2 == nk) aim(nx);
+            issue(kt + 2 - nk, buf);
+          }
+        }
+      });
+      buf ^= 1;
+    };
+    static_for<nk>([&](auto kt) {
+      if (nk > 1) buf = kt & 1;
+      stage(kt);
+    });
+    static_for<TL::FM>([&](auto f) {
+      const int m = token(t, wm * TL::TM + 16 * f + l16);
+      if (m < M) {
+        const QkvRow rr = out.row(m, t.n0);
+        static_for<TL::FN / 2>([&](auto p) {
+          const f32x4_t y0 = acc[f][2 * p] + bv[2 * p], y1 = acc[f][2 * p + 1] + bv[2 * p + 1];
+          const int c = c0 + 32 * p;
+          if (part == 2) {
+            const int vs = out.vstride();
+            bf16* dst = rr.base + (size_t)c * vs;
+            static_for<8>([&](auto e) { dst[(size_t)e * vs] = f2bf(e < 4 ? y0[int(e) % 4] : y1[int(e) % 4]); });
+          } else {
+            const int off = part == 0 ? c : (c >> out.dsh) * out.kstride() + (c & ((1 << out.dsh) - 1));
+            *reinterpret_cast<u32x4_t*>(rr.base + off) = pack_bf8(y0, y1);
+          }
+        });
+      }
+    });
+    if (last) return;
+    t = nx;
   }
-  qkv_list_launch<TL, 0>(M, C, xh, tiles, ntiles, w, out, s);
 }
 
-template <class TL, class Out>
-static void qkv_launch(int M, int C, int S, const bf16* xh, const uint8_t* flag, const int32_t* wcount,
+// Two-row-tile blocks run several tiles each, two blocks per CU; one-row-tile blocks, of which
+// there are few rounds, run one tile each (with several each: 17.7 -> 20.9 us at 32,400 rows of
+// 256, 11.1 -> 12.9 us at 6,480).
+template <class TL, int C, class Out>
+static void qkv_launch(int M, const bf16* xh, const int32_t* tiles, const int32_t* ntiles, int kv_all,
                        const bf16* w, const Out& out, hipStream_t s) {
   static bool attr = false;
   if (!attr) {
-    allow_lds(qkv_kernel<TL, Out>, TL::LDS_BYTES);
+    allow_lds(qkv_kernel<TL, Out, C>, TL::LDS_BYTES);
     attr = true;
   }
-  const int grid = xcd_grid((M + TL::BM - 1) / TL::BM, 3 * C / TL::BN);
-  qkv_kernel<TL, Out><<<grid, TL::THREADS, TL::LDS_BYTES, s>>>(M, C, S, xh, flag, wcount, w, out);
+  const int mt = (M + TL::BM - 1) / TL::BM;
+  const int most = xcd_grid(mt, C / TL::BN) + xcd_grid(mt, 2 * C / TL::BN);
+  const int grid = TL::BM == ROW_TILE || most < 512 ? most : 512;
+  qkv_kernel<TL, Out, C><<<grid, TL::THREADS, TL::LDS_BYTES, s>>>(M, xh, tiles, ntiles, kv_all, w, out);
+}
+
+// One instantiation per network width, with the k loop unrolled (0.8 % per clip at
+// 5 x 240 x 432 and 5 x 720 x 1280, timed back to back on one GPU).  BIG_M rows and more take two row tiles per block (4 wavefronts of 64 x 64 outputs:
+// half the operand bytes from L2 and LDS per product), fewer rows one row tile on 8
+// wavefronts, so that there are blocks for every CU.
+template <class Out>
+static void qkv_by_c(int M, int C, const bf16* xh, const int32_t* tiles, const int32_t* ntiles, int kv_all,
+                     const bf16* w, const Out& out, hipStream_t s) {
+  using Big = GemmTile<128, 128, 2, 2, 2>;
+  using Small = GemmTile<64, 128, 2, 4, 2>;
+  using Narrow = GemmTile<64, 64, 2, 2, 2>;
+  const bool big = M >= BIG_M;
+  switch (C) {
+    case 64: return qkv_launch<Narrow, 64>(M, xh, tiles, ntiles, kv_all, w, out, s);
+    case 128:
+      return big ? qkv_launch<Big, 128>(M, xh, tiles, ntiles, kv_all, w, out, s)
+                 : qkv_launch<Small, 128>(M, xh, tiles, ntiles, kv_all, w, out, s);
+    case 256:
+      return big ? qkv_launch<Big, 256>(M, xh, tiles, ntiles, kv_all, w, out, s)
+                 : qkv_launch<Small, 256>(M, xh, tiles, ntiles, kv_all, w, out, s);
+    case 384:
+      return big ? qkv_launch<Big, 384>(M, xh, tiles, ntiles, kv_all, w, out, s)
+                 : qkv_launch<Small, 384>(M, xh, tiles, ntiles, kv_all, w, out, s);
+    default: return;  // rejected by the callers (resid_ln_supported)
+  }
 }
 
 // log2 of a power of two (head widths 32 and 64 are the ones the attention kernels take)
@@ -245,26 +354,14 @@ void launch_qkv_bf16(const Geo& g, int C, int heads, int Spad, int spv, const bf
                      hipStream_t s) {
   if (g.N <= 0) return;
   const QkvOut out{bias, q, k, vt, C, log2_pow2(C / heads), heads, Spad, g.S, spv};
-  // 8 wavefronts per 64 x 128 tile below BIG_M tokens (0.6 % faster per clip at 5 x 240 x 432,
-  // 1 % slower at 5 x 720 x 1280, timed back to back on one GPU)
-  if (C % 128 == 0 && g.N < BIG_M)
-    qkv_list_by_c<GemmTile<64, 128, 2, 4, 2>>(g.N, C, xh, tiles, ntiles, w, out, s);
-  else if (C % 128 == 0)
-    qkv_list_by_c<GemmTile<64, 128, 2, 2, 2>>(g.N, C, xh, tiles, ntiles, w, out, s);
-  else
-    qkv_list_by_c<GemmTile<64, 64, 2, 2, 3>>(g.N, C, xh, tiles, ntiles, w, out, s);
+  qkv_by_c(g.N, C, xh, tiles, ntiles, 0, w, out, s);
 }
 
-void launch_qkv_stream(const Geo& g, int C, int heads, const bf16* xh, const uint8_t* flag, const bf16* w,
-                       const float* bias, bf16* q, const StreamTable& tab, hipStream_t s) {
+void launch_qkv_stream(const Geo& g, int C, int heads, const bf16* xh, const int32_t* tiles, const int32_t* ntiles,
+                       const bf16* w, const float* bias, bf16* q, const StreamTable& tab, hipStream_t s) {
   if (g.N <= 0) return;
   const StreamQkvOut out{bias, q, tab, C, log2_pow2(C / heads), heads, g.S, g.nwh * g.nww};
-  if (C % 128 == 0 && g.N >= BIG_M)
-    qkv_launch<GemmTile<256, 128, 4, 2, 2>>(g.N, C, g.S, xh, flag, nullptr, w, out, s);
-  else if (C % 128 == 0)
-    qkv_launch<GemmTile<64, 128, 2, 2, 2>>(g.N, C, g.S, xh, flag, nullptr, w, out, s);
-  else
-    qkv_launch<GemmTile<64, 64, 2, 2, 3>>(g.N, C, g.S, xh, flag, nullptr, w, out, s);
+  qkv_by_c(g.N, C, xh, tiles, ntiles, 1, w, out, s);
 }
 
 // ------------------------------------------------------------------------------------------
