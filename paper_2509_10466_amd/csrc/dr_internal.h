@@ -240,9 +240,9 @@ void launch_decode(const Geo& g, int C, const float* x, const int32_t* idx, cons
 void launch_copy_unmasked(size_t npix, const float* frames, const uint8_t* masks, float* out,
                           hipStream_t s);
 
-// FP32 path
+// FP32 path (copy: receives the rows read, unchanged)
 void launch_ln_f32(const float* x, const int32_t* rows, const int32_t* nrows_dev, int nrows_max,
-                   int C, const float* g, const float* b, float* y, hipStream_t s);
+                   int C, const float* g, const float* b, float* y, hipStream_t s, float* copy = nullptr);
 enum EpiKind { EPI_STORE = 0, EPI_GELU = 1, EPI_RESID = 2 };
 // Y = A[rows] W^T + bias, A f32 [*, K] (row stride K), W f32 [Nout, K].
 //   EPI_STORE: Y[r, :] stored to out (row stride Nout)
@@ -251,6 +251,10 @@ enum EpiKind { EPI_STORE = 0, EPI_GELU = 1, EPI_RESID = 2 };
 void launch_gemm_f32(const float* A, const int32_t* arows, const int32_t* m_dev, int m_max,
                      int K, const float* W, const float* bias, int Nout, int epi, float* out,
                      const int32_t* res_rows, hipStream_t s);
+// the same with operands rounded to bf16
+void launch_gemm_bf16ops(const float* A, const int32_t* arows, const int32_t* m_dev, int m_max, int K,
+                         const float* W, const float* bias, int Nout, int epi, float* out,
+                         const int32_t* res_rows, hipStream_t s);
 void launch_attn_f32(const Geo& g, int C, int heads, const float* q, const float* kv,
                      const int32_t* woff, float* o, hipStream_t s);
 // FP32 window attention on the matrix cores, with each query's and head's softmax (max, sum)
@@ -268,8 +272,9 @@ inline int ln_bwd_blocks(int n_max) { return (n_max + LNB_ROWS - 1) / LNB_ROWS; 
 // FP8 path (OCP e4m3 operands, per-tensor scales s = amax/448, FP32 accumulation)
 bool fp8_supported(int C, int R);
 void launch_quantize_fp8(const float* in, uint8_t* out, size_t n, float inv_scale, hipStream_t s);
-// as launch_quantize_fp8 with the scale read from device memory (values / *scale)
-void launch_quantize_fp8_dev(const float* in, uint8_t* out, size_t n, const float* scale, hipStream_t s);
+// the weights of all blocks, scales (8 per block) read from device memory
+void launch_quantize_fp8_weights(const float* const* ptrs, const size_t* counts, int blocks, size_t nCC, size_t nRC,
+                                 const float* scales, uint8_t* out, hipStream_t s);
 void launch_zero_f32(float* p, int n, hipStream_t s);
 // LayerNorm of rows (affine) into bf16 rows plus the call's amax: rows given -> compact output
 // rows r < *nrows_dev from x[rows[r]]; else rows r < nrows_max of windows with queries.

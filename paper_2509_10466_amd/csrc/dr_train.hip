@@ -10,6 +10,7 @@
 // max / sum.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <vector>
 
@@ -20,23 +21,20 @@ using namespace dr;
 namespace dr {
 void launch_gather_rows(const float* X, const int32_t* rows, const int32_t* n_dev, int n_max, int C, float* Y, hipStream_t s);
 void launch_scatter_rows(const float* Y, const int32_t* rows, const int32_t* n_dev, int n_max, int C, float* X, hipStream_t s);
-void launch_gelu_fwd(const float* h, const int32_t* n_dev, int n_max, int R, float* a, hipStream_t s);
-void launch_gelu_bwd(const float* h, const float* da, const int32_t* n_dev, int n_max, int R, float* dh, hipStream_t s);
 void launch_attn_train_dq(const Geo& g, int C, int heads, const float* q, const float* kv, const float* dout,
                           const float2* stats, const int32_t* woff, float* dq, float* dsum, hipStream_t s);
 void launch_attn_train_dkv(const Geo& g, int C, int heads, const float* q, const float* kv, const float* dout,
                            const float2* stats, const float* dsum, const int32_t* woff, float* dkv, hipStream_t s);
-void launch_ln_bwd(const float* x, const int32_t* rows, const int32_t* n_dev, int n_max, int C, const float* g,
-                   const float* dy, float* dx, int accumulate, int dst_compact, float* part, hipStream_t s);
-void launch_sum_parts(const float* part, int nparts, const int32_t* n_dev, int rows_per, int width, float* out,
-                      int accumulate, hipStream_t s);
+void launch_gelu_fwd(const float* h, const int32_t* n_dev, int n_max, int R, float* a, hipStream_t s);
+void launch_gelu_bwd(const float* h, const int32_t* n_dev, int n_max, int R, float* d, float* a, hipStream_t s);
+void launch_ln_bwd(const float* x, const int32_t* n_dev, int n_max, int C, const float* g, const float* dy,
+                   const float* acc, float* dx, float* part, hipStream_t s);
+void launch_sum_parts(const float* part, int nparts, size_t stride, const int32_t* n_dev, int rows_per, int width,
+                      float* out, hipStream_t s);
 void launch_tn_f32(const float* A, const int32_t* arow, int lda, const float* B, const int32_t* brow, int ldb,
                        const int32_t* M_dev, int M_max, int I, int J, float* part, hipStream_t s);
 void launch_tn_bf16ops(const float* A, const int32_t* arow, int lda, const float* B, const int32_t* brow, int ldb,
                        const int32_t* M_dev, int M_max, int I, int J, float* part, hipStream_t s);
-void launch_gemm_bf16ops(const float* A, const int32_t* arows, const int32_t* m_dev, int m_max, int K,
-                         const float* W, const float* bias, int Nout, int epi, float* out,
-                         const int32_t* res_rows, hipStream_t s);
 void launch_colsum_partial(const float* B, int ldb, const int32_t* M_dev, int M_max, int J, float* part, hipStream_t s);
 void launch_patches(const Geo& g, const float* frames, const uint8_t* masks, float* P, hipStream_t s);
 void launch_decoder_full(const Geo& g, int C, const float* z, const float* dw, const float* db, float* pred, hipStream_t s);
@@ -92,7 +90,7 @@ struct dr_train {
   // forward scratch
   float* x = nullptr;
   // reverse-pass scratch
-  float *a = nullptr, *dx = nullptr, *dx2 = nullptr, *dx1 = nullptr, *da = nullptr, *dh = nullptr, *dn2 = nullptr,
+  float *a = nullptr, *dx = nullptr, *dx2 = nullptr, *dx1 = nullptr, *dh = nullptr, *dn2 = nullptr,
         *dout = nullptr, *dq = nullptr, *dkv = nullptr, *du = nullptr, *dsum = nullptr, *dyt = nullptr,
         *dz = nullptr, *part = nullptr, *lnpart = nullptr, *zeros = nullptr, *tmp = nullptr;
   // loss scratch (allocated once)
@@ -107,7 +105,7 @@ static void free_list(std::vector<void*>& l) {
 
 static void scratch_free(dr_train* t) {
   free_list(t->allocs);
-  t->x = t->a = t->dx = t->dx2 = t->dx1 = t->da = t->dh = t->dn2 = t->dout = t->dq = t->dkv = t->du = t->dsum =
+  t->x = t->a = t->dx = t->dx2 = t->dx1 = t->dh = t->dn2 = t->dout = t->dq = t->dkv = t->du = t->dsum =
       t->dyt = t->dz = t->part = t->lnpart = t->zeros = t->tmp = nullptr;
   t->cap = 0;
 }
@@ -170,7 +168,6 @@ static dr_status scratch_reserve(dr_ctx* c, dr_train* t, const Geo& g) {
     t->dx = (float*)A(N * C * 4);
     t->dx2 = (float*)A(N * C * 4);
     t->dx1 = (float*)A(N * C * 4);
-    t->da = (float*)A(N * R * 4);
     t->dh = (float*)A(N * R * 4);
     t->dn2 = (float*)A(N * C * 4);
     t->dout = (float*)A(N * C * 4);
@@ -180,7 +177,7 @@ static dr_status scratch_reserve(dr_ctx* c, dr_train* t, const Geo& g) {
     t->dsum = (float*)A(N * H * 4);
     t->dyt = (float*)A(N * 48 * 4);
     t->dz = (float*)A(N * C * 4);
-    t->part = (float*)A((size_t)tn_chunks((int)N) * R * C * 4);
+    t->part = (float*)A((size_t)tn_chunks((int)N) * std::max(R, 2 * C) * C * 4);
     t->lnpart = (float*)A((size_t)ln_bwd_blocks((int)N) * 2 * C * 4);
     t->zeros = (float*)A((2 * C + R + 64) * 4);
     t->tmp = (float*)A((R * C + 64) * 4);
@@ -311,8 +308,7 @@ static dr_status train_forward_into(dr_ctx* c, dr_train* t, dr_saved* sv, const 
   for (int l = 0; l < n.cfg.blocks; ++l) {
     const BlockW& b = n.blk[l];
     TrainBlock& tb = sv->blk[l];
-    HIP_OK(c, hipMemcpyAsync(tb.x_in, t->x, (size_t)N * C * 4, hipMemcpyDeviceToDevice, s));
-    launch_ln_f32(t->x, nullptr, nullptr, N, C, b.ln1g, b.ln1b, tb.u, s);
+    launch_ln_f32(t->x, nullptr, nullptr, N, C, b.ln1g, b.ln1b, tb.u, s, tb.x_in);
     train_gemm(b16, tb.u, nullptr, nullptr, N, C, b.wkv, b.bkv, 2 * C, EPI_STORE, tb.kv, nullptr, s);
     train_gemm(b16, tb.u, sv->idx, sv->nq, N, C, b.wq, b.bq, C, EPI_STORE, tb.q, nullptr, s);
     launch_attn_train_fwd(g, C, heads, tb.q, tb.kv, sv->woff, tb.o, tb.stats, s);
@@ -324,8 +320,7 @@ static dr_status train_forward_into(dr_ctx* c, dr_train* t, dr_saved* sv, const 
     train_gemm(b16, t->a, nullptr, sv->nq, N, R, b.w2, b.b2, C, EPI_RESID, t->x, sv->idx, s);
     KCHECK("block");
   }
-  HIP_OK(c, hipMemcpyAsync(sv->xf, t->x, (size_t)N * C * 4, hipMemcpyDeviceToDevice, s));
-  launch_ln_f32(t->x, nullptr, nullptr, N, C, n.lnfg, n.lnfb, sv->z, s);
+  launch_ln_f32(t->x, nullptr, nullptr, N, C, n.lnfg, n.lnfb, sv->z, s, sv->xf);
   launch_decoder_full(g, C, sv->z, n.dec_w, n.dec_b, sv->pred, s);
   KCHECK("decoder");
   HIP_OK(c, hipMemcpyAsync(pred, sv->pred, (size_t)N * 16 * 12, hipMemcpyDeviceToDevice, s));
@@ -387,13 +382,13 @@ extern "C" dr_status dr_saved_free(dr_ctx* c, dr_saved* sv) {
 static void tn_grad(dr_train* t, bool bf16, const float* A, const int32_t* arow, int lda, const float* Bm, const int32_t* brow,
                     int ldb, const int32_t* M_dev, int M_max, int I, int J, float* out, hipStream_t s) {
   (bf16 ? launch_tn_bf16ops : launch_tn_f32)(A, arow, lda, Bm, brow, ldb, M_dev, M_max, I, J, t->part, s);
-  launch_sum_parts(t->part, tn_chunks(M_max), M_dev, TN_CHUNK, I * J, out, 0, s);
+  launch_sum_parts(t->part, tn_chunks(M_max), (size_t)I * J, M_dev, TN_CHUNK, I * J, out, s);
 }
 
 static void colsum_grad(dr_train* t, const float* Bm, int ldb, const int32_t* M_dev, int M_max, int J, float* out,
                         hipStream_t s) {
   launch_colsum_partial(Bm, ldb, M_dev, M_max, J, t->part, s);
-  launch_sum_parts(t->part, tn_chunks(M_max), M_dev, TN_CHUNK, J, out, 0, s);
+  launch_sum_parts(t->part, tn_chunks(M_max), J, M_dev, TN_CHUNK, J, out, s);
 }
 
 // [C][48] (k = (ky*4 + kx)*3 + ch) -> [C][3][4][4]
@@ -447,8 +442,8 @@ extern "C" dr_status dr_train_backward(dr_ctx* c, dr_saved* sv, const float* dpr
   fold48_kernel<<<1, 64, 0, s>>>(t->tmp, G + po.db);
   train_gemm(b16, t->dyt, nullptr, nullptr, N, 48, W(n.dec_w), t->zeros, C, EPI_STORE, t->dz, nullptr, s);
   // final LayerNorm
-  launch_ln_bwd(sv->xf, nullptr, nullptr, N, C, W(n.lnfg), t->dz, t->dx, 0, 0, t->lnpart, s);
-  launch_sum_parts(t->lnpart, ln_bwd_blocks(N), nullptr, LNB_ROWS, 2 * C, G + po.lnfg, 0, s);  // lnf.g then lnf.b
+  launch_ln_bwd(sv->xf, nullptr, N, C, W(n.lnfg), t->dz, nullptr, t->dx, t->lnpart, s);
+  launch_sum_parts(t->lnpart, ln_bwd_blocks(N), 2 * C, nullptr, LNB_ROWS, 2 * C, G + po.lnfg, s);  // lnf.g then lnf.b
   KCHECK("decoder backward");
   for (int l = n.cfg.blocks - 1; l >= 0; --l) {
     const BlockW& b = n.blk[l];
@@ -456,17 +451,16 @@ extern "C" dr_status dr_train_backward(dr_ctx* c, dr_saved* sv, const float* dpr
     const ParamOffsets::B& pb = po.blk[l];
     // x2 = x1 + W2 GELU(W1 LN2(x1) + b1) + b2 on the query rows
     launch_gather_rows(t->dx, sv->idx, sv->nq, N, C, t->dx2, s);
-    launch_gelu_fwd(tb.hpre, sv->nq, N, R, t->a, s);
+    // dh = (dx2 W2) GELU'(hpre) and GELU(hpre) again
+    train_gemm(b16, t->dx2, nullptr, sv->nq, N, C, W(b.w2T), t->zeros, R, EPI_STORE, t->dh, nullptr, s);
+    launch_gelu_bwd(tb.hpre, sv->nq, N, R, t->dh, t->a, s);
     tn_grad(t, b16, t->dx2, nullptr, C, t->a, nullptr, R, sv->nq, N, C, R, G + pb.w2, s);
     colsum_grad(t, t->dx2, C, sv->nq, N, C, G + pb.b2, s);
-    train_gemm(b16, t->dx2, nullptr, sv->nq, N, C, W(b.w2T), t->zeros, R, EPI_STORE, t->da, nullptr, s);
-    launch_gelu_bwd(tb.hpre, t->da, sv->nq, N, R, t->dh, s);
     tn_grad(t, b16, t->dh, nullptr, R, tb.n2, nullptr, C, sv->nq, N, R, C, G + pb.w1, s);
     colsum_grad(t, t->dh, R, sv->nq, N, R, G + pb.b1, s);
     train_gemm(b16, t->dh, nullptr, sv->nq, N, R, W(b.w1T), t->zeros, C, EPI_STORE, t->dn2, nullptr, s);
-    HIP_OK(c, hipMemcpyAsync(t->dx1, t->dx2, (size_t)N * C * 4, hipMemcpyDeviceToDevice, s));
-    launch_ln_bwd(tb.x1, nullptr, sv->nq, N, C, W(b.ln2g), t->dn2, t->dx1, 1, 1, t->lnpart, s);
-    launch_sum_parts(t->lnpart, ln_bwd_blocks(N), sv->nq, LNB_ROWS, 2 * C, G + pb.ln2g, 0, s);  // ln2.g then ln2.b
+    launch_ln_bwd(tb.x1, sv->nq, N, C, W(b.ln2g), t->dn2, t->dx2, t->dx1, t->lnpart, s);
+    launch_sum_parts(t->lnpart, ln_bwd_blocks(N), 2 * C, sv->nq, LNB_ROWS, 2 * C, G + pb.ln2g, s);  // ln2.g then ln2.b
     // x1 = x + Wo O + bo
     tn_grad(t, b16, t->dx1, nullptr, C, tb.o, nullptr, C, sv->nq, N, C, C, G + pb.wo, s);
     colsum_grad(t, t->dx1, C, sv->nq, N, C, G + pb.bo, s);
@@ -480,15 +474,18 @@ extern "C" dr_status dr_train_backward(dr_ctx* c, dr_saved* sv, const float* dpr
     // Q, K, V projections
     tn_grad(t, b16, t->dq, nullptr, C, tb.u, sv->idx, C, sv->nq, N, C, C, G + pb.wq, s);
     colsum_grad(t, t->dq, C, sv->nq, N, C, G + pb.bq, s);
-    tn_grad(t, b16, t->dkv, nullptr, 2 * C, tb.u, nullptr, C, nullptr, N, C, C, G + pb.wk, s);
-    tn_grad(t, b16, t->dkv + C, nullptr, 2 * C, tb.u, nullptr, C, nullptr, N, C, C, G + pb.wv, s);
-    colsum_grad(t, t->dkv, 2 * C, nullptr, N, C, G + pb.bk, s);
-    colsum_grad(t, t->dkv + C, 2 * C, nullptr, N, C, G + pb.bv, s);
+    // W_k and W_v (and their biases) in one reduction over the same rows of u
+    (b16 ? launch_tn_bf16ops : launch_tn_f32)(t->dkv, nullptr, 2 * C, tb.u, nullptr, C, nullptr, N, 2 * C, C, t->part, s);
+    launch_sum_parts(t->part, tn_chunks(N), (size_t)2 * C * C, nullptr, TN_CHUNK, C * C, G + pb.wk, s);
+    launch_sum_parts(t->part + (size_t)C * C, tn_chunks(N), (size_t)2 * C * C, nullptr, TN_CHUNK, C * C, G + pb.wv, s);
+    launch_colsum_partial(t->dkv, 2 * C, nullptr, N, 2 * C, t->part, s);
+    launch_sum_parts(t->part, tn_chunks(N), 2 * C, nullptr, TN_CHUNK, C, G + pb.bk, s);
+    launch_sum_parts(t->part + C, tn_chunks(N), 2 * C, nullptr, TN_CHUNK, C, G + pb.bv, s);
     train_gemm(b16, t->dkv, nullptr, nullptr, N, 2 * C, W(b.wkvT), t->zeros, C, EPI_STORE, t->du, nullptr, s);
     train_gemm(b16, t->dq, nullptr, sv->nq, N, C, W(b.wqT), t->zeros, C, EPI_RESID, t->du, sv->idx, s);
     // LN1
-    launch_ln_bwd(tb.x_in, nullptr, nullptr, N, C, W(b.ln1g), t->du, t->dx, 1, 0, t->lnpart, s);
-    launch_sum_parts(t->lnpart, ln_bwd_blocks(N), nullptr, LNB_ROWS, 2 * C, G + pb.ln1g, 0, s);  // ln1.g then ln1.b
+    launch_ln_bwd(tb.x_in, nullptr, N, C, W(b.ln1g), t->du, t->dx, t->dx, t->lnpart, s);
+    launch_sum_parts(t->lnpart, ln_bwd_blocks(N), 2 * C, nullptr, LNB_ROWS, 2 * C, G + pb.ln1g, s);  // ln1.g then ln1.b
     KCHECK("qkv backward");
   }
   // patch embedding

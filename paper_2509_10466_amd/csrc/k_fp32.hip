@@ -21,7 +21,7 @@ template <typename OutT>
 __global__ void __launch_bounds__(256) ln_kernel(const float* __restrict__ x, const int32_t* __restrict__ rows,
                                                  const int32_t* __restrict__ nrows_dev, int nrows_max, int C,
                                                  const float* __restrict__ g, const float* __restrict__ b,
-                                                 OutT* __restrict__ y) {
+                                                 OutT* __restrict__ y, float* __restrict__ copy) {
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int nrows = nrows_dev ? nrows_dev[0] : nrows_max;
@@ -35,6 +35,8 @@ __global__ void __launch_bounds__(256) ln_kernel(const float* __restrict__ x, co
     v[e] = xr[lane + 64 * e];
     s += v[e];
   }
+  if (copy)
+    for (int e = 0; e < per; ++e) copy[(size_t)r * C + lane + 64 * e] = v[e];
   const float mean = wave_sum(s) / C;
   float q = 0.f;
   for (int e = 0; e < per; ++e) {
@@ -50,9 +52,9 @@ __global__ void __launch_bounds__(256) ln_kernel(const float* __restrict__ x, co
 }
 
 void launch_ln_f32(const float* x, const int32_t* rows, const int32_t* nrows_dev, int nrows_max,
-                   int C, const float* g, const float* b, float* y, hipStream_t s) {
+                   int C, const float* g, const float* b, float* y, hipStream_t s, float* copy) {
   if (nrows_max <= 0) return;
-  ln_kernel<float><<<(nrows_max + 3) / 4, 256, 0, s>>>(x, rows, nrows_dev, nrows_max, C, g, b, y);
+  ln_kernel<float><<<(nrows_max + 3) / 4, 256, 0, s>>>(x, rows, nrows_dev, nrows_max, C, g, b, y, copy);
 }
 
 

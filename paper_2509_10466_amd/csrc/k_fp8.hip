@@ -64,8 +64,7 @@ __device__ __forceinline__ float wave_max_abs(float v) { return wave_max(fabsf(v
 // elementwise quantisation (weights at load, and the test hook)
 // ------------------------------------------------------------------------------------------
 __global__ void quantize_fp8_kernel(const float* __restrict__ in, uint8_t* __restrict__ out, size_t n,
-                                    float inv_scale, const float* __restrict__ scale) {
-  if (scale) inv_scale = 1.0f / *scale;
+                                    float inv_scale) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; 2 * i < n; i += (size_t)gridDim.x * blockDim.x) {
     const float a = in[2 * i] * inv_scale;
     const float b = (2 * i + 1 < n) ? in[2 * i + 1] * inv_scale : 0.f;
@@ -78,13 +77,27 @@ __global__ void quantize_fp8_kernel(const float* __restrict__ in, uint8_t* __res
 void launch_quantize_fp8(const float* in, uint8_t* out, size_t n, float inv_scale, hipStream_t s) {
   size_t grid = (n / 2 + 256) / 256;
   if (grid > 8192) grid = 8192;
-  if (grid) quantize_fp8_kernel<<<(unsigned)grid, 256, 0, s>>>(in, out, n, inv_scale, nullptr);
+  if (grid) quantize_fp8_kernel<<<(unsigned)grid, 256, 0, s>>>(in, out, n, inv_scale);
 }
 
-void launch_quantize_fp8_dev(const float* in, uint8_t* out, size_t n, const float* scale, hipStream_t s) {
-  size_t grid = (n / 2 + 256) / 256;
-  if (grid > 8192) grid = 8192;
-  if (grid) quantize_fp8_kernel<<<(unsigned)grid, 256, 0, s>>>(in, out, n, 1.f, scale);
+// the six weight tensors of every block (blockIdx.y = 6 l + k) into their places in out: per
+// block four of nCC values, then two of nRC
+__global__ void quantize_fp8_weights_kernel(const float* const* __restrict__ ptrs, const size_t* __restrict__ counts,
+                                            size_t nCC, size_t nRC, const float* __restrict__ scales,
+                                            uint8_t* __restrict__ out) {
+  const int t = blockIdx.y, l = t / 6, k = t % 6;
+  const float* in = ptrs[t];
+  const size_t n = counts[t];  // a multiple of 4
+  uint32_t* dst = reinterpret_cast<uint32_t*>(out + l * (4 * nCC + 2 * nRC) + (k < 4 ? k * nCC : 4 * nCC + (k - 4) * nRC));
+  const float inv = 1.0f / scales[8 * l + k];
+  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; 4 * i < n; i += (size_t)gridDim.x * blockDim.x)
+    dst[i] = f32x2_to_fp8(in[4 * i] * inv, in[4 * i + 1] * inv) |
+             (f32x2_to_fp8(in[4 * i + 2] * inv, in[4 * i + 3] * inv) << 16);
+}
+
+void launch_quantize_fp8_weights(const float* const* ptrs, const size_t* counts, int blocks, size_t nCC, size_t nRC,
+                                 const float* scales, uint8_t* out, hipStream_t s) {
+  quantize_fp8_weights_kernel<<<dim3(32, 6 * blocks), 256, 0, s>>>(ptrs, counts, nCC, nRC, scales, out);
 }
 
 __global__ void zero_f32_kernel(float* p, int n) {

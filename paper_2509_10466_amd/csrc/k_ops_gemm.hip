@@ -223,22 +223,20 @@ __global__ void __launch_bounds__(TL::THREADS, 2) gemm_ops_kernel(const float* _
 // as 0.4 of its bound, the most a clip's mask is expected to cover.
 static bool ops_big(long long blocks, bool dev_rows) { return (dev_rows ? 2 * blocks / 5 : blocks) >= 512; }
 
-template <class TL>
-static void gemm_ops_launch(const float* A, const int32_t* arows, const int32_t* m_dev, int m_max, int K, const float* W,
-                            const float* bias, int Nout, int epi, float* out, const int32_t* res_rows, hipStream_t s) {
-  const int grid = xcd_grid((m_max + TL::BM - 1) / TL::BM, (Nout + TL::BN - 1) / TL::BN);
-  gemm_ops_kernel<TL><<<grid, TL::THREADS, 0, s>>>(A, arows, m_dev, m_max, K, W, bias, Nout, epi, out, res_rows);
-}
-
 template <int NP>
 static void gemm_ops(const float* A, const int32_t* arows, const int32_t* m_dev, int m_max, int K, const float* W,
                      const float* bias, int Nout, int epi, float* out, const int32_t* res_rows, hipStream_t s) {
   if (m_max <= 0) return;
+  auto run = [&](auto tl) {
+    using TL = decltype(tl);
+    const int grid = xcd_grid((m_max + TL::BM - 1) / TL::BM, (Nout + TL::BN - 1) / TL::BN);
+    gemm_ops_kernel<TL><<<grid, TL::THREADS, 0, s>>>(A, arows, m_dev, m_max, K, W, bias, Nout, epi, out, res_rows);
+  };
   const long long blocks = (long long)((m_max + 127) / 128) * ((Nout + 127) / 128);
   if (ops_big(blocks, m_dev != nullptr))
-    gemm_ops_launch<OpsTile<128, 128, NP>>(A, arows, m_dev, m_max, K, W, bias, Nout, epi, out, res_rows, s);
+    run(OpsTile<128, 128, NP>());
   else
-    gemm_ops_launch<OpsTile<64, 64, NP>>(A, arows, m_dev, m_max, K, W, bias, Nout, epi, out, res_rows, s);
+    run(OpsTile<64, 64, NP>());
 }
 
 void launch_gemm_f32(const float* A, const int32_t* arows, const int32_t* m_dev, int m_max, int K, const float* W,

@@ -2,6 +2,8 @@
 // network.  Weight gradients are reductions over tokens; they are computed deterministically
 // (fixed chunks of rows, then the chunk partials summed in order), so a gradient does not
 // depend on launch timing or on which other clips share the batch.
+#include <algorithm>
+
 #include "dr_device.h"
 #include "dr_internal.h"
 
@@ -44,123 +46,161 @@ void launch_scatter_rows(const float* Y, const int32_t* rows, const int32_t* n_d
 }
 
 // ------------------------------------------------------------------------------------------
-// elementwise: a = GELU(h);  dh = da * GELU'(h),  GELU'(z) = Phi(z) + z phi(z)
+// elementwise, four values per thread: a = GELU(h); and in the reverse pass d = d GELU'(h),
+// GELU'(z) = Phi(z) + z phi(z), with a = GELU(h) again from the same error function (as two
+// passes 35 + 58 us at 18,800 rows of 1,024; in the epilogue of the product that makes d, which
+// its two blocks per CU do not hide, about 100 us)
 // ------------------------------------------------------------------------------------------
-__global__ void gelu_fwd_kernel(const float* __restrict__ h, const int32_t* __restrict__ n_dev, int R,
-                                float* __restrict__ a) {
-  const size_t n = (size_t)n_dev[0] * R;
-  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x)
-    a[e] = gelu_erf(h[e]);
-}
-
-__global__ void gelu_bwd_kernel(const float* __restrict__ h, const float* __restrict__ da,
-                                const int32_t* __restrict__ n_dev, int R, float* __restrict__ dh) {
-  const size_t n = (size_t)n_dev[0] * R;
+__global__ void __launch_bounds__(256) gelu_fwd_kernel(const float* __restrict__ h, const int32_t* __restrict__ n_dev,
+                                                       int R, float* __restrict__ a) {
+  const size_t n = (size_t)n_dev[0] * R / 4;
   for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x) {
-    const float z = h[e];
-    const float cdf = 0.5f * (1.0f + erff(z * 0.70710678118654752f));
-    const float pdf = 0.3989422804014327f * expf(-0.5f * z * z);
-    dh[e] = da[e] * (cdf + z * pdf);
+    const float4 z = reinterpret_cast<const float4*>(h)[e];
+    reinterpret_cast<float4*>(a)[e] = make_float4(gelu_erf(z.x), gelu_erf(z.y), gelu_erf(z.z), gelu_erf(z.w));
   }
 }
 
+__device__ __forceinline__ void gelu_grad(float z, float& d, float& a) {
+  const float e1 = 1.0f + erff(z * 0.70710678118654752f);
+  a = 0.5f * z * e1;
+  const float cdf = 0.5f * e1;
+  const float pdf = 0.3989422804014327f * expf(-0.5f * z * z);
+  d *= cdf + z * pdf;
+}
+
+__global__ void __launch_bounds__(256) gelu_bwd_kernel(const float* __restrict__ h, const int32_t* __restrict__ n_dev,
+                                                       int R, float* __restrict__ d, float* __restrict__ a) {
+  const size_t n = (size_t)n_dev[0] * R / 4;
+  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < n; e += (size_t)gridDim.x * blockDim.x) {
+    const float4 z = reinterpret_cast<const float4*>(h)[e];
+    float4 g = reinterpret_cast<const float4*>(d)[e], y;
+    gelu_grad(z.x, g.x, y.x);
+    gelu_grad(z.y, g.y, y.y);
+    gelu_grad(z.z, g.z, y.z);
+    gelu_grad(z.w, g.w, y.w);
+    reinterpret_cast<float4*>(d)[e] = g;
+    reinterpret_cast<float4*>(a)[e] = y;
+  }
+}
+
+static unsigned gelu_grid(int n_max, int R) { return (unsigned)std::min<size_t>(((size_t)n_max * R / 4 + 255) / 256, 8192); }
+
 void launch_gelu_fwd(const float* h, const int32_t* n_dev, int n_max, int R, float* a, hipStream_t s) {
-  size_t grid = ((size_t)n_max * R + 255) / 256;
-  if (grid > 8192) grid = 8192;
-  if (grid) gelu_fwd_kernel<<<(unsigned)grid, 256, 0, s>>>(h, n_dev, R, a);
+  if (n_max > 0) gelu_fwd_kernel<<<gelu_grid(n_max, R), 256, 0, s>>>(h, n_dev, R, a);
 }
 
-void launch_gelu_bwd(const float* h, const float* da, const int32_t* n_dev, int n_max, int R, float* dh,
-                     hipStream_t s) {
-  size_t grid = ((size_t)n_max * R + 255) / 256;
-  if (grid > 8192) grid = 8192;
-  if (grid) gelu_bwd_kernel<<<(unsigned)grid, 256, 0, s>>>(h, da, n_dev, R, dh);
+void launch_gelu_bwd(const float* h, const int32_t* n_dev, int n_max, int R, float* d, float* a, hipStream_t s) {
+  if (n_max > 0) gelu_bwd_kernel<<<gelu_grid(n_max, R), 256, 0, s>>>(h, n_dev, R, d, a);
 }
 
 // ------------------------------------------------------------------------------------------
-// LayerNorm backward, one wavefront per row r < *n (or n_max): rows of x at rows[r] (or r);
-// dx[r] = rstd * (dxh - mean(dxh) - xh * mean(dxh * xh)), dxh = dy * gamma, written or added
-// (accumulate) at dst row (rows ? rows[r] : r) or compact r (dst_compact).  dgamma/dbeta
-// partials per block of 64 rows: part[blk][0..C) = sum dy*xh, part[blk][C..2C) = sum dy.
+// LayerNorm backward, one wavefront per row r < *n_dev (or n_max):
+// dx[r] = (acc ? acc[r] : 0) + rstd * (dxh - mean(dxh) - xh * mean(dxh * xh)), dxh = dy * gamma
+// (acc may be dx).  dgamma/dbeta partials per block of LNB_ROWS rows:
+// part[blk][0..C) = sum dy*xh, part[blk][C..2C) = sum dy.  PER = C / 64 values per lane, fixed
+// at compile time for the network widths so that a row's loads are issued together.
 // ------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) ln_bwd_kernel(const float* __restrict__ x, const int32_t* __restrict__ rows,
-                                                     const int32_t* __restrict__ n_dev, int n_max, int C,
-                                                     const float* __restrict__ g, const float* __restrict__ dy,
-                                                     float* __restrict__ dx, int accumulate, int dst_compact,
+template <int PER>
+__global__ void __launch_bounds__(256) ln_bwd_kernel(const float* __restrict__ x, const int32_t* __restrict__ n_dev,
+                                                     int n_max, int C, const float* __restrict__ g,
+                                                     const float* __restrict__ dy, const float* acc, float* dx,
                                                      float* __restrict__ part) {
+  // every rounding is as written here, whatever the unrolling
+#pragma clang fp contract(off)
   extern __shared__ float red[];  // [4][2C]
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int n = n_dev ? n_dev[0] : n_max;
   if (blockIdx.x * LNB_ROWS >= n) return;  // uniform per block
-  const int per = C / 64;
-  float pg[16], pb[16];
-  for (int e = 0; e < per; ++e) pg[e] = pb[e] = 0.f;
+  constexpr int MAXP = PER ? PER : 16;
+  const int per = PER ? PER : C / 64;
+  float pg[MAXP], pb[MAXP], gm[MAXP];
+#pragma unroll
+  for (int e = 0; e < MAXP; ++e)
+    if (e < per) {
+      pg[e] = pb[e] = 0.f;
+      gm[e] = g[lane + 64 * e];
+    }
   for (int rr = 0; rr < LNB_ROWS / 4; ++rr) {
     const int r = blockIdx.x * LNB_ROWS + rr * 4 + wv;
     if (r >= n) break;
-    const size_t src = rows ? (size_t)rows[r] : (size_t)r;
-    const float* xr = x + src * C;
-    const float* dyr = dy + (size_t)r * C;
-    float v[16], d[16];
+    const size_t at = (size_t)r * C + lane;
+    float v[MAXP], d[MAXP], o[MAXP];
     float s = 0.f;
-    for (int e = 0; e < per; ++e) {
-      v[e] = xr[lane + 64 * e];
-      s += v[e];
-    }
+#pragma unroll
+    for (int e = 0; e < MAXP; ++e)
+      if (e < per) {
+        v[e] = x[at + 64 * e];
+        d[e] = dy[at + 64 * e];
+        o[e] = acc ? acc[at + 64 * e] : 0.f;
+      }
+#pragma unroll
+    for (int e = 0; e < MAXP; ++e)
+      if (e < per) s += v[e];
     const float mean = wave_sum(s) / C;
     float q = 0.f;
-    for (int e = 0; e < per; ++e) {
-      const float t = v[e] - mean;
-      q += t * t;
-    }
+#pragma unroll
+    for (int e = 0; e < MAXP; ++e)
+      if (e < per) {
+        const float t = v[e] - mean;
+        q = fmaf(t, t, q);
+      }
     const float rstd = rsqrtf(wave_sum(q) / C + 1e-5f);
     float s1 = 0.f, s2 = 0.f;
-    for (int e = 0; e < per; ++e) {
-      const int c = lane + 64 * e;
-      const float xh = (v[e] - mean) * rstd;
-      const float dyv = dyr[c];
-      d[e] = dyv * g[c];
-      s1 += d[e];
-      s2 += d[e] * xh;
-      pg[e] += dyv * xh;
-      pb[e] += dyv;
-      v[e] = xh;
-    }
+#pragma unroll
+    for (int e = 0; e < MAXP; ++e)
+      if (e < per) {
+        const float xh = (v[e] - mean) * rstd;
+        const float dyv = d[e];
+        d[e] = dyv * gm[e];
+        s1 = fmaf(dyv, gm[e], s1);
+        s2 = fmaf(d[e], xh, s2);
+        pg[e] = fmaf(dyv, xh, pg[e]);
+        pb[e] += dyv;
+        v[e] = xh;
+      }
     s1 = wave_sum(s1) / C;
     s2 = wave_sum(s2) / C;
-    float* out = dx + (dst_compact ? (size_t)r : src) * C;
-    for (int e = 0; e < per; ++e) {
-      const int c = lane + 64 * e;
-      const float val = rstd * (d[e] - s1 - v[e] * s2);
-      out[c] = accumulate ? out[c] + val : val;
-    }
+#pragma unroll
+    for (int e = 0; e < MAXP; ++e)
+      if (e < per) {
+        const float val = rstd * fmaf(-v[e], s2, d[e] - s1);
+        dx[at + 64 * e] = acc ? o[e] + val : val;
+      }
   }
   // fixed-order block reduction of the dgamma / dbeta partials
-  for (int e = 0; e < per; ++e) {
-    red[wv * 2 * C + lane + 64 * e] = pg[e];
-    red[wv * 2 * C + C + lane + 64 * e] = pb[e];
-  }
+#pragma unroll
+  for (int e = 0; e < MAXP; ++e)
+    if (e < per) {
+      red[wv * 2 * C + lane + 64 * e] = pg[e];
+      red[wv * 2 * C + C + lane + 64 * e] = pb[e];
+    }
   __syncthreads();
   for (int c = threadIdx.x; c < 2 * C; c += blockDim.x)
     part[(size_t)blockIdx.x * 2 * C + c] = red[c] + red[2 * C + c] + red[4 * C + c] + red[6 * C + c];
 }
 
-void launch_ln_bwd(const float* x, const int32_t* rows, const int32_t* n_dev, int n_max, int C, const float* g,
-                   const float* dy, float* dx, int accumulate, int dst_compact, float* part, hipStream_t s) {
-  const int blocks = (n_max + LNB_ROWS - 1) / LNB_ROWS;
+void launch_ln_bwd(const float* x, const int32_t* n_dev, int n_max, int C, const float* g, const float* dy,
+                   const float* acc, float* dx, float* part, hipStream_t s) {
+  const int blocks = ln_bwd_blocks(n_max);
   if (blocks <= 0) return;
-  ln_bwd_kernel<<<blocks, 256, 4 * 2 * C * sizeof(float), s>>>(x, rows, n_dev, n_max, C, g, dy, dx, accumulate,
-                                                              dst_compact, part);
+  const size_t lds = 4 * 2 * C * sizeof(float);
+  switch (C) {
+    case 64: ln_bwd_kernel<1><<<blocks, 256, lds, s>>>(x, n_dev, n_max, C, g, dy, acc, dx, part); break;
+    case 128: ln_bwd_kernel<2><<<blocks, 256, lds, s>>>(x, n_dev, n_max, C, g, dy, acc, dx, part); break;
+    case 256: ln_bwd_kernel<4><<<blocks, 256, lds, s>>>(x, n_dev, n_max, C, g, dy, acc, dx, part); break;
+    case 384: ln_bwd_kernel<6><<<blocks, 256, lds, s>>>(x, n_dev, n_max, C, g, dy, acc, dx, part); break;
+    default: ln_bwd_kernel<0><<<blocks, 256, lds, s>>>(x, n_dev, n_max, C, g, dy, acc, dx, part); break;
+  }
 }
 
-// out[c] (+)= sum of part[b][c] over the parts in use: all nparts, or with n_dev the first
+// out[c] = sum of part[b * stride + c] over the parts in use: all nparts, or with n_dev the first
 // ceil(*n_dev / rows_per).  Four interleaved sums (part b of the first nparts / 4 * 4 in sum
 // b mod 4, the rest in sum 0) combined in a fixed order, so the result depends on nothing but
 // the values.  The four sums of a column run in four threads, each with eight loads in flight:
 // as one chain per column this took 25 us on average in a 4-clip training step, mostly latency.
 __global__ void __launch_bounds__(256) sum_parts_kernel(const float* __restrict__ part, int nparts,
-                                                        const int32_t* __restrict__ n_dev, int rows_per, int width,
-                                                        float* __restrict__ out, int accumulate) {
+                                                        size_t stride, const int32_t* __restrict__ n_dev, int rows_per,
+                                                        int width, float* __restrict__ out) {
   __shared__ float sums[4][64];
   const int col = threadIdx.x & 63, q = threadIdx.x >> 6, c = blockIdx.x * 64 + col;
   const int used = n_dev ? min(nparts, (n_dev[0] + rows_per - 1) / rows_per) : nparts;
@@ -172,26 +212,25 @@ __global__ void __launch_bounds__(256) sum_parts_kernel(const float* __restrict_
     for (; b + 28 < end; b += 32) {
       float v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = p[(size_t)(b + 4 * u) * width];
+      for (int u = 0; u < 8; ++u) v[u] = p[(b + 4 * u) * stride];
 #pragma unroll
       for (int u = 0; u < 8; ++u) a += v[u];
     }
-    for (; b < end; b += 4) a += p[(size_t)b * width];
+    for (; b < end; b += 4) a += p[b * stride];
     if (q == 0)
-      for (b = n4; b < used; ++b) a += p[(size_t)b * width];
+      for (b = n4; b < used; ++b) a += p[b * stride];
   }
   sums[q][col] = a;
   __syncthreads();
   if (q == 0 && c < width) {
-    const float acc = (sums[0][col] + sums[1][col]) + (sums[2][col] + sums[3][col]);
-    out[c] = accumulate ? out[c] + acc : acc;
+    out[c] = (sums[0][col] + sums[1][col]) + (sums[2][col] + sums[3][col]);
   }
 }
 
-void launch_sum_parts(const float* part, int nparts, const int32_t* n_dev, int rows_per, int width, float* out,
-                      int accumulate, hipStream_t s) {
+void launch_sum_parts(const float* part, int nparts, size_t stride, const int32_t* n_dev, int rows_per, int width,
+                      float* out, hipStream_t s) {
   if (width <= 0) return;
-  sum_parts_kernel<<<(width + 63) / 64, 256, 0, s>>>(part, nparts, n_dev, rows_per, width, out, accumulate);
+  sum_parts_kernel<<<(width + 63) / 64, 256, 0, s>>>(part, nparts, stride, n_dev, rows_per, width, out);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -275,24 +314,60 @@ void launch_patches(const Geo& g, const float* frames, const uint8_t* masks, flo
   patches_kernel<<<(unsigned)grid, 256, 0, s>>>(g, frames, masks, P);
 }
 
-__global__ void decoder_full_kernel(Geo g, int C, const float* __restrict__ z, const float* __restrict__ dw,
-                                    const float* __restrict__ db, float* __restrict__ pred) {
-  for (size_t e = blockIdx.x * (size_t)blockDim.x + threadIdx.x; e < (size_t)g.N * 48; e += (size_t)gridDim.x * blockDim.x) {
-    const int n = (int)(e / 48), k = (int)(e % 48);
-    const int pix = k / 3, c = k - 3 * pix, ky = pix >> 2, kx = pix & 3;
-    const float* zr = z + (size_t)n * C;
-    float acc = db[c];
-    for (int i = 0; i < C; ++i) acc = fmaf(zr[i], dw[i * 48 + k], acc);
-    const size_t px = tok_pixel(g, n) + (size_t)ky * g.W + kx;
-    pred[px * 3 + c] = 1.0f / (1.0f + expf(-acc));
+// Full-frame decoder: 48 threads (one per output of a token) x 4 groups of DEC_TOK tokens per
+// block; z rows and the weight's 48 columns go through LDS in 64-channel slices, and a weight
+// value serves DEC_TOK tokens (one output per thread, reading its row and column from memory,
+// took 605 us at 129,600 tokens of 256).  Each output is one chain of fused multiply-adds over
+// the channels in order.
+constexpr int DEC_TOK = 8;
+__global__ void __launch_bounds__(192) decoder_full_kernel(Geo g, int C, const float* __restrict__ z,
+                                                           const float* __restrict__ dw, const float* __restrict__ db,
+                                                           float* __restrict__ pred) {
+  __shared__ __align__(16) float zs[4 * DEC_TOK][64];
+  __shared__ float ws[64][48];
+  const int t = threadIdx.x, grp = t / 48, k = t - 48 * grp;
+  const int pix = k / 3, c = k - 3 * pix, ky = pix >> 2, kx = pix & 3;
+  const int n0 = blockIdx.x * 4 * DEC_TOK;
+  float acc[DEC_TOK];
+#pragma unroll
+  for (int u = 0; u < DEC_TOK; ++u) acc[u] = db[c];
+  for (int i0 = 0; i0 < C; i0 += 64) {
+    for (int e = t; e < 4 * DEC_TOK * 16; e += 192) {
+      const int row = e >> 4, col = (e & 15) * 4;
+      *reinterpret_cast<float4*>(&zs[row][col]) =
+          *reinterpret_cast<const float4*>(z + (size_t)min(n0 + row, g.N - 1) * C + i0 + col);
+    }
+    for (int e = t; e < 64 * 48; e += 192) (&ws[0][0])[e] = dw[(size_t)i0 * 48 + e];
+    __syncthreads();
+#pragma unroll 4
+    for (int i = 0; i < 64; i += 4) {
+      float w[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = ws[i + e][k];
+#pragma unroll
+      for (int u = 0; u < DEC_TOK; ++u) {
+        const float4 zv = *reinterpret_cast<const float4*>(&zs[grp * DEC_TOK + u][i]);
+        acc[u] = fmaf(zv.x, w[0], acc[u]);
+        acc[u] = fmaf(zv.y, w[1], acc[u]);
+        acc[u] = fmaf(zv.z, w[2], acc[u]);
+        acc[u] = fmaf(zv.w, w[3], acc[u]);
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int u = 0; u < DEC_TOK; ++u) {
+    const int n = n0 + grp * DEC_TOK + u;
+    if (n < g.N) {
+      const size_t px = tok_pixel(g, n) + (size_t)ky * g.W + kx;
+      pred[px * 3 + c] = 1.0f / (1.0f + expf(-acc[u]));
+    }
   }
 }
 
 void launch_decoder_full(const Geo& g, int C, const float* z, const float* dw, const float* db, float* pred,
                          hipStream_t s) {
-  size_t grid = ((size_t)g.N * 48 + 255) / 256;
-  if (grid > 16384) grid = 16384;
-  decoder_full_kernel<<<(unsigned)grid, 256, 0, s>>>(g, C, z, dw, db, pred);
+  if (g.N > 0) decoder_full_kernel<<<(g.N + 4 * DEC_TOK - 1) / (4 * DEC_TOK), 192, 0, s>>>(g, C, z, dw, db, pred);
 }
 
 __global__ void dec_grad_tok_kernel(Geo g, const float* __restrict__ pred, const float* __restrict__ dpred,
@@ -351,11 +426,20 @@ __global__ void l1_partial_kernel(const float* __restrict__ pred, const float* _
 
 __global__ void l1_final_kernel(const float* __restrict__ part, int nb, float w_in, float w_out,
                                 float* __restrict__ acc, float* __restrict__ loss) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  double s[4] = {0, 0, 0, 0};
-  for (int b = 0; b < nb; ++b)
-    for (int k = 0; k < 4; ++k) s[k] += part[b * 4 + k];
-  for (int k = 0; k < 4; ++k) acc[k] = (float)s[k];
+  // the four sums run in four threads, over partials that the block has brought to LDS
+  __shared__ float sh[4 * L1_BLOCKS];
+  __shared__ double s[4];
+  for (int e = threadIdx.x; e < 4 * nb; e += blockDim.x) sh[e] = part[e];
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    double t = 0;
+#pragma unroll 16
+    for (int b = 0; b < nb; ++b) t += sh[b * 4 + threadIdx.x];
+    s[threadIdx.x] = t;
+    acc[threadIdx.x] = (float)t;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
   double L = 0.0;
   if (s[2] > 0) L += w_in * s[0] / s[2];
   if (s[3] > 0) L += w_out * s[1] / s[3];
@@ -377,7 +461,7 @@ __global__ void l1_grad_kernel(const float* __restrict__ pred, const float* __re
 void launch_l1_loss(const float* pred, const float* gt, const uint8_t* masks, size_t npix, float w_in, float w_out,
                     float* part, float* acc, float* loss, float* dpred, hipStream_t s) {
   l1_partial_kernel<<<L1_BLOCKS, 256, 0, s>>>(pred, gt, masks, npix, part);
-  l1_final_kernel<<<1, 64, 0, s>>>(part, L1_BLOCKS, w_in, w_out, acc, loss);
+  l1_final_kernel<<<1, 256, 0, s>>>(part, L1_BLOCKS, w_in, w_out, acc, loss);
   if (dpred) {
     size_t grid = (3 * npix + 255) / 256;
     if (grid > 8192) grid = 8192;

@@ -29,7 +29,6 @@
 
 namespace dr {
 
-constexpr int TA_THREADS = 256;
 constexpr int TA_MAX_S = 304;  // keys (or queries) per window the LDS tiles hold
 
 __device__ __forceinline__ f32x4_t mfma_f32_4(float a, float b, const f32x4_t& c) {
@@ -57,7 +56,7 @@ __device__ __forceinline__ const float4& ta_chunk(const float* t, int s, int c) 
 }
 
 // rows [0, npad) of a [rows][DH] tile from global rows src + i * ld (i < n), zero beyond n
-template <int DH>
+template <int DH, int TA_THREADS>
 __device__ __forceinline__ void ta_stage(const float* __restrict__ src, size_t ld, int n, int npad, float* dst) {
   constexpr int NCH = DH / 4;
   for (int e = threadIdx.x; e < npad * NCH; e += TA_THREADS) {
@@ -107,7 +106,12 @@ __device__ __forceinline__ f32x4_t ta_dot_tile(const float* At, int a0, const fl
 // D[channel 16 dt + 4 g' + r'][l % 16].
 template <int DH>
 __device__ __forceinline__ void ta_accum_T(const float* Tt, int x0, const float (&x)[4], f32x4_t (&acc)[DH / 16]) {
-  const int lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
+  // the lane passes through an empty asm so that the sixteen addresses below are recomputed for
+  // every tile rather than kept in registers over the kernel (fwd at 240 keys: 113 instead of
+  // 355 registers, which is what lets 16 wavefronts share the tiles)
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+  const int l16 = lane & 15, g = lane >> 4;
   float a[4][DH / 16];
 #pragma unroll
   for (int r = 0; r < 4; ++r)
@@ -124,7 +128,7 @@ __device__ __forceinline__ void ta_accum_T(const float* Tt, int x0, const float 
 // ------------------------------------------------------------------------------------------
 // forward with (m, l)
 // ------------------------------------------------------------------------------------------
-template <int DH, int NT>
+template <int DH, int NT, int TA_THREADS>
 __global__ void __launch_bounds__(TA_THREADS) attn_train_fwd_kernel(int S, int C, int heads, const float* __restrict__ q,
                                                                     const float* __restrict__ kv,
                                                                     const int32_t* __restrict__ woff,
@@ -137,8 +141,8 @@ __global__ void __launch_bounds__(TA_THREADS) attn_train_fwd_kernel(int S, int C
   if (nq == 0) return;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l16 = lane & 15, g = lane >> 4;
   const float* kbase = kv + (size_t)w * S * 2 * C + h * DH;
-  ta_stage<DH>(kbase, 2 * C, S, 16 * NT, Ks);
-  ta_stage<DH>(kbase + C, 2 * C, S, 16 * NT, Vs);
+  ta_stage<DH, TA_THREADS>(kbase, 2 * C, S, 16 * NT, Ks);
+  ta_stage<DH, TA_THREADS>(kbase + C, 2 * C, S, 16 * NT, Vs);
   __syncthreads();
   const float scale = rsqrtf((float)DH);
   for (int qt = wv; qt * 16 < nq; qt += TA_THREADS / 64) {
@@ -190,7 +194,7 @@ __global__ void __launch_bounds__(TA_THREADS) attn_train_fwd_kernel(int S, int C
 // ------------------------------------------------------------------------------------------
 // reverse, query side: dQ and D = rowsum(P dP)
 // ------------------------------------------------------------------------------------------
-template <int DH, int NT>
+template <int DH, int NT, int TA_THREADS>
 __global__ void __launch_bounds__(TA_THREADS) attn_train_dq_kernel(int S, int C, int heads, const float* __restrict__ q,
                                                                    const float* __restrict__ kv,
                                                                    const float* __restrict__ dout,
@@ -205,8 +209,8 @@ __global__ void __launch_bounds__(TA_THREADS) attn_train_dq_kernel(int S, int C,
   if (nq == 0) return;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l16 = lane & 15, g = lane >> 4;
   const float* kbase = kv + (size_t)w * S * 2 * C + h * DH;
-  ta_stage<DH>(kbase, 2 * C, S, 16 * NT, Ks);
-  ta_stage<DH>(kbase + C, 2 * C, S, 16 * NT, Vs);
+  ta_stage<DH, TA_THREADS>(kbase, 2 * C, S, 16 * NT, Ks);
+  ta_stage<DH, TA_THREADS>(kbase + C, 2 * C, S, 16 * NT, Vs);
   __syncthreads();
   const float scale = rsqrtf((float)DH);
   for (int qt = wv; qt * 16 < nq; qt += TA_THREADS / 64) {
@@ -255,7 +259,7 @@ __global__ void __launch_bounds__(TA_THREADS) attn_train_dq_kernel(int S, int C,
 // ------------------------------------------------------------------------------------------
 // reverse, key side: dK and dV of every key of the window (zero without queries)
 // ------------------------------------------------------------------------------------------
-template <int DH, int NT>
+template <int DH, int NT, int TA_THREADS>
 __global__ void __launch_bounds__(TA_THREADS) attn_train_dkv_kernel(int S, int C, int heads, const float* __restrict__ q,
                                                                     const float* __restrict__ kv,
                                                                     const float* __restrict__ dout,
@@ -274,8 +278,8 @@ __global__ void __launch_bounds__(TA_THREADS) attn_train_dkv_kernel(int S, int C
   const int q0 = woff[w], nq = woff[w + 1] - q0;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, l16 = lane & 15, g = lane >> 4;
   const int nqt = (nq + 15) / 16;
-  ta_stage<DH>(q + (size_t)q0 * C + h * DH, C, nq, 16 * nqt, Qs);
-  ta_stage<DH>(dout + (size_t)q0 * C + h * DH, C, nq, 16 * nqt, Gs);
+  ta_stage<DH, TA_THREADS>(q + (size_t)q0 * C + h * DH, C, nq, 16 * nqt, Qs);
+  ta_stage<DH, TA_THREADS>(dout + (size_t)q0 * C + h * DH, C, nq, 16 * nqt, Gs);
   for (int i = threadIdx.x; i < 16 * nqt; i += TA_THREADS) {
     // padding queries: m = +inf makes their probabilities 0
     const float2 st = i < nq ? stats[(size_t)(q0 + i) * heads + h] : make_float2(INFINITY, 1.f);
@@ -339,18 +343,23 @@ static void ta_launch(int which, const Geo& g, int C, int heads, const float* q,
   const size_t kvb = (size_t)2 * 16 * NT * DH * 4;
   const size_t dkvb = kvb + (size_t)3 * 16 * NT * 4;
   const dim3 grid(g.nwin * heads);
+  // LDS holds one workgroup per CU at 240 keys, so a workgroup has as many wavefronts as its
+  // registers allow: 16 (4 per SIMD) up to 128 registers, 8 up to 256, else 4
   if (which == 0) {
+    constexpr int TH = NT > 15 ? 512 : 1024;
     static bool a = false;
-    if (!a) { ta_allow(attn_train_fwd_kernel<DH, NT>, kvb); a = true; }
-    attn_train_fwd_kernel<DH, NT><<<grid, TA_THREADS, kvb, s>>>(g.S, C, heads, q, kv, woff, o, stats);
+    if (!a) { ta_allow(attn_train_fwd_kernel<DH, NT, TH>, kvb); a = true; }
+    attn_train_fwd_kernel<DH, NT, TH><<<grid, TH, kvb, s>>>(g.S, C, heads, q, kv, woff, o, stats);
   } else if (which == 1) {
+    constexpr int TH = NT > 15 ? 256 : 512;
     static bool a = false;
-    if (!a) { ta_allow(attn_train_dq_kernel<DH, NT>, kvb); a = true; }
-    attn_train_dq_kernel<DH, NT><<<grid, TA_THREADS, kvb, s>>>(g.S, C, heads, q, kv, dout, cstats, woff, dq, dsum);
+    if (!a) { ta_allow(attn_train_dq_kernel<DH, NT, TH>, kvb); a = true; }
+    attn_train_dq_kernel<DH, NT, TH><<<grid, TH, kvb, s>>>(g.S, C, heads, q, kv, dout, cstats, woff, dq, dsum);
   } else {
+    constexpr int TH = 1024;
     static bool a = false;
-    if (!a) { ta_allow(attn_train_dkv_kernel<DH, NT>, dkvb); a = true; }
-    attn_train_dkv_kernel<DH, NT><<<grid, TA_THREADS, dkvb, s>>>(g.S, C, heads, q, kv, dout, cstats, cdsum, woff, dkv);
+    if (!a) { ta_allow(attn_train_dkv_kernel<DH, NT, TH>, dkvb); a = true; }
+    attn_train_dkv_kernel<DH, NT, TH><<<grid, TH, dkvb, s>>>(g.S, C, heads, q, kv, dout, cstats, cdsum, woff, dkv);
   }
 }
 
