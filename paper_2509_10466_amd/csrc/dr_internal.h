@@ -285,7 +285,8 @@ void launch_ln_rows_amax(const float* x, const int32_t* rows, const int32_t* nro
 // vt [win][head][dh][spv]; row tiles from the lists of launch_window_order
 void launch_qkv_fp8(const Geo& g, int C, int heads, int Spad, int spv, const bf16* u, const int32_t* tiles,
                     const int32_t* ntiles, const uint8_t* w, const float* wscale, const float* bias,
-                    const float* amax_u, float qscale, bf16* q, bf16* k, bf16* vt, hipStream_t s);
+                    const float* amax_u, float qscale, const uint8_t* flag, bf16* q, bf16* k, bf16* vt,
+                    hipStream_t s);
 // first MLP linear + GELU over compact rows u [*m_dev][C] -> h [.][R], amax of h
 void launch_fc1_fp8(int m_max, const int32_t* m_dev, int C, int R, const bf16* u, const uint8_t* w, const float* s_w,
                     const float* bias, const float* amax_u, bf16* h, float* amax_h, hipStream_t s);

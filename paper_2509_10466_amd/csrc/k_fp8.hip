@@ -17,8 +17,11 @@
 // MFMA 16x16x128 f8f6f4 operands: lane l supplies row/column (l % 16) with 32 consecutive
 // k values in group (l / 16); A and B use the same k slots, so any k order common to both is
 // legal.  The double-rate hazard rule of the BF16 kernels applies: MFMA groups are fenced.
+#include <algorithm>
+
 #include "dr_device.h"
 #include "dr_internal.h"
+#include "gemm_core.h"
 
 namespace dr {
 
@@ -197,12 +200,28 @@ void launch_ln_rows_amax(const float* x, const int32_t* rows, const int32_t* nro
 
 // ------------------------------------------------------------------------------------------
 // FP8 GEMM over bf16 rows: Y[m, n] = s_a (e4m3(A/s_a) . e4m3(W)^T)[m, n], handed with s_a to
-// an epilogue (which applies s_w, the bias and the destination).  256 threads = 2 x 2 waves,
-// tile 64 x 128, 128-wide k stages, A converted bf16 -> e4m3 while it is staged into LDS.
-// Rows: M = *m_dev when given, else m_host.  Without a tile list a tile runs only if
-// epi.need(m, n0) holds for one of its rows; with one (Q/K/V), block x takes row tile
-// tiles[list * mt + x] of list epi.list(n0) (lists built with the window order, ROW_TILE rows).
+// an epilogue (which applies s_w, the bias and the destination).  Rows: M = *m_dev when given,
+// else m_host.
+//
+// gemm_fp8_rows_kernel: a block holds 64 rows of A in LDS, quantised once, and runs column
+// tiles of 128 (all of them, or a share where there are too few row tiles to fill the chip:
+// blockIdx.y of gridDim.y) with the weight streaming through a 3-stage ring of 128-wide k
+// stages by direct global->LDS loads.  (A 64 x 128 tile per block quantised its A rows again
+// for every column tile, through registers, and the weight too: 450 us for Q/K/V and 232 us
+// for the first MLP linear at 5 x 720 x 1280, against about 140 and 70 us for their bytes.)
+// Rows of 128 bytes hold their 16-byte chunks at f8_pos(c) ^ (row & 7): a lane reads chunks
+// 2 kg and 2 kg + 1, and f8_pos makes the four lane groups of a read neighbours, as they are in
+// the bf16 core (with c ^ (row & 7) every second cycle of the reads was a bank conflict).
+//
+// gemm_fp8_kernel: 64 x 128 tile per block, two LDS stages, A quantised while staged; for K too
+// large for the LDS.
 // ------------------------------------------------------------------------------------------
+// 8 bf16 values times inv_sa -> 8 e4m3 bytes
+__device__ __forceinline__ uint2 bf16x8_to_fp8(const u32x4_t& v, float inv_sa) {
+  auto two = [&](uint32_t w) { return f32x2_to_fp8(bf2f(w & 0xffff) * inv_sa, bf2f(w >> 16) * inv_sa); };
+  return make_uint2(two(v.x) | (two(v.y) << 16), two(v.z) | (two(v.w) << 16));
+}
+
 constexpr int F8_BK = 128;          // fp8 elements per stage = one MFMA k step
 constexpr int F8_WST = F8_BK + 16;  // stage row stride in bytes
 // Tile: BM x BN outputs, WM x WN wavefronts (each TM x TN), two LDS stages of 128-wide k.
@@ -217,32 +236,20 @@ struct F8Tile {
   static_assert(TM % 16 == 0 && TN % 16 == 0, "fragment multiples");
   static_assert(BM * 16 % THREADS == 0 && BN * 8 % THREADS == 0, "whole chunks per thread");
 };
-using F8Small = F8Tile<64, 128, 2, 2>;  // 4 wavefronts; the Q/K/V row-tile lists use its 64 rows
-static_assert(F8Small::BM == ROW_TILE, "row tiles are listed in ROW_TILE units");
+using F8Small = F8Tile<64, 128, 2, 2>;
 
 template <class TL, class Epi>
 __global__ void __launch_bounds__(TL::THREADS) gemm_fp8_kernel(const bf16* __restrict__ A,
                                                                const int32_t* __restrict__ m_dev, int m_host, int K,
                                                                const uint8_t* __restrict__ W,
-                                                               const float* __restrict__ amax_a,
-                                                               const int32_t* __restrict__ tiles,
-                                                               const int32_t* __restrict__ ntiles, Epi epi) {
+                                                               const float* __restrict__ amax_a, Epi epi) {
   extern __shared__ __align__(16) uint8_t f8_lds[];
   uint8_t(*As)[TL::BM][F8_WST] = reinterpret_cast<uint8_t(*)[TL::BM][F8_WST]>(f8_lds);
   uint8_t(*Ws)[TL::BN][F8_WST] = reinterpret_cast<uint8_t(*)[TL::BN][F8_WST]>(f8_lds + 2 * TL::BM * F8_WST);
   const int M = m_dev ? m_dev[0] : m_host;
   const int n0 = blockIdx.y * TL::BN;
-  int m0 = blockIdx.x * TL::BM;
-  if (tiles) {  // (launched with F8Small only)
-    const int l = epi.list(n0);
-    if ((int)blockIdx.x >= ntiles[l]) return;
-    m0 = tiles[l * ((m_host + TL::BM - 1) / TL::BM) + blockIdx.x] * TL::BM;
-  } else {
-    if (m0 >= M) return;
-    int nd = 0;
-    if ((int)threadIdx.x < TL::BM && m0 + (int)threadIdx.x < M) nd = epi.need(m0 + threadIdx.x, n0);
-    if (!__syncthreads_or(nd)) return;
-  }
+  const int m0 = blockIdx.x * TL::BM;
+  if (m0 >= M) return;
   const float sa = scale_of(amax_a);
   const float inv_sa = 1.0f / sa;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
@@ -271,13 +278,7 @@ __global__ void __launch_bounds__(TL::THREADS) gemm_fp8_kernel(const bf16* __res
     for (int c = 0; c < TL::LA; ++c) {
       const int id = t + TL::THREADS * c;
       const int row = id >> 4, col = (id & 15) * 8;
-      const uint32_t w4[4] = {ra[c].x, ra[c].y, ra[c].z, ra[c].w};
-      uint32_t lo = 0, hi = 0;
-      lo = f32x2_to_fp8(bf2f(w4[0] & 0xffff) * inv_sa, bf2f(w4[0] >> 16) * inv_sa) |
-           (f32x2_to_fp8(bf2f(w4[1] & 0xffff) * inv_sa, bf2f(w4[1] >> 16) * inv_sa) << 16);
-      hi = f32x2_to_fp8(bf2f(w4[2] & 0xffff) * inv_sa, bf2f(w4[2] >> 16) * inv_sa) |
-           (f32x2_to_fp8(bf2f(w4[3] & 0xffff) * inv_sa, bf2f(w4[3] >> 16) * inv_sa) << 16);
-      *reinterpret_cast<uint2*>(&As[buf][row][col]) = make_uint2(lo, hi);
+      *reinterpret_cast<uint2*>(&As[buf][row][col]) = bf16x8_to_fp8(ra[c], inv_sa);
     }
 #pragma unroll
     for (int c = 0; c < TL::LW; ++c) {
@@ -341,11 +342,161 @@ __global__ void __launch_bounds__(TL::THREADS) gemm_fp8_kernel(const bf16* __res
   epi.finish();
 }
 
-template <class TL, class Epi>
-static void gemm_fp8_launch(const bf16* A, const int32_t* m_dev, int m_max, int K, int Nout, const uint8_t* W,
-                            const float* amax_a, const Epi& epi, hipStream_t s, const int32_t* tiles = nullptr,
-                            const int32_t* ntiles = nullptr) {
+__device__ __forceinline__ int f8_pos(int c) { return (c >> 1) | ((c & 1) << 2); }
+__device__ __forceinline__ int f8_chunk(int pos) { return ((pos & 3) << 1) | (pos >> 2); }
+
+// NW wavefronts in 2 (rows) x NW / 2 (columns).
+template <int NW>
+struct F8Rows {
+  static constexpr int BM = 64, BN = 128, THREADS = 64 * NW, WN = NW / 2;  // (THREADS: without the loader)
+  static constexpr int TM = BM / 2, TN = BN / WN, FM = TM / 16, FN = TN / 16, ST = 3;
+  static constexpr int STAGE = BN * F8_BK;             // bytes
+  static constexpr int LOADS = STAGE / 1024;           // 1 KB loads per stage
+};
+static_assert(F8Rows<4>::BM == ROW_TILE, "row tiles are listed in ROW_TILE units");
+
+// With lists (Q/K/V: K/V row tiles listed with the window order, their Q columns only where a
+// token of the tile is flagged) block x takes listed tile x, else rows 64 x ..
+//
+// The weight is queued by a wavefront of its own (the last), which waits for its loads alone:
+// vector-memory operations complete in order for a wavefront's counter, so a wavefront that
+// also stores results would wait for those stores before it can see the next stage.
+template <int NW, class Epi>
+__global__ void __launch_bounds__(64 * NW + 64, NW == 4 ? 4 : 3) gemm_fp8_rows_kernel(const bf16* __restrict__ A,
+                                                                const int32_t* __restrict__ m_dev, int m_host, int K,
+                                                                int Nout, const uint8_t* __restrict__ W,
+                                                                const float* __restrict__ amax_a,
+                                                                const int32_t* __restrict__ tiles,
+                                                                const int32_t* __restrict__ ntiles,
+                                                                const uint8_t* __restrict__ flag, Epi epi) {
+  using TL = F8Rows<NW>;
+  extern __shared__ __align__(16) uint8_t f8_lds[];
+  const int nk = K / F8_BK;
+  uint8_t* As = f8_lds;                     // [nk][64][128]
+  uint8_t* Ws = f8_lds + nk * TL::BM * F8_BK;  // [ST][128][128]
+  const int M = m_dev ? m_dev[0] : m_host;
+  const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wm = wv / TL::WN, wn = wv % TL::WN, l16 = lane & 15, kg = lane >> 4;
+  int m0 = blockIdx.x * TL::BM, ct0 = 0;
+  if (tiles) {
+    if ((int)blockIdx.x >= ntiles[1]) return;
+    m0 = tiles[(m_host + ROW_TILE - 1) / ROW_TILE + blockIdx.x] * ROW_TILE;
+    const int any = t < TL::BM && m0 + t < M && flag[m0 + t] != 0;
+    if (!__syncthreads_or(any)) ct0 = epi.skip() / TL::BN;
+  } else if (m0 >= M) {
+    return;
+  }
+  const int nct = Nout / TL::BN - ct0;
+  const int first = ct0 + nct * blockIdx.y / gridDim.y, last = ct0 + nct * (blockIdx.y + 1) / gridDim.y;
+  const int total = (last - first) * nk;  // weight stages
+  if (total <= 0) return;
+  if (wv == NW) {  // the loader: barrier k opens stage k, behind which slot k - 1 is free
+    const int lrow = lane >> 3;
+    const uint32_t woff = lrow * K + f8_chunk((lane & 7) ^ lrow) * 16;
+    int ict = first, ikb = 0, islot = 0;
+    auto queue = [&] {
+      const uint8_t* src = W + (size_t)ict * TL::BN * K + ikb * F8_BK;
+      static_for<TL::LOADS>([&](auto c) {
+        dma16(src + (size_t)8 * c * K + woff, reinterpret_cast<bf16*>(Ws + islot * TL::STAGE + 8 * c * F8_BK));
+      });
+      if (++ikb == nk) {
+        ikb = 0;
+        ++ict;
+      }
+      islot = islot == TL::ST - 1 ? 0 : islot + 1;
+    };
+    queue();
+    if (total > 1) queue();
+    for (int k = 0; k < total; ++k) {
+      if (k + 1 < total)
+        vm_wait_barrier<TL::LOADS>();
+      else
+        vm_wait_barrier<0>();
+      if (k + 2 < total) queue();
+    }
+    return;
+  }
+  const float sa = scale_of(amax_a);
+  const float inv_sa = 1.0f / sa;
+  constexpr int LA = TL::BM * 16 / TL::THREADS;  // 16-byte bf16 chunks of A per thread and k stage
+#pragma unroll 3
+  for (int kb = 0; kb < nk; ++kb) {
+    u32x4_t ra[LA];
+    static_for<LA>([&](auto c) {
+      const int id = t + TL::THREADS * c, row = id >> 4, col = id & 15, m = m0 + row;
+      ra[c] = *reinterpret_cast<const u32x4_t*>(A + (size_t)min(m, M - 1) * K + kb * F8_BK + col * 8);
+    });
+    static_for<LA>([&](auto c) {
+      const int id = t + TL::THREADS * c, row = id >> 4, col = id & 15;
+      *reinterpret_cast<uint2*>(As + (kb * TL::BM + row) * F8_BK + ((f8_pos(col >> 1) ^ (row & 7)) * 16) + (col & 1) * 8) =
+          bf16x8_to_fp8(ra[c], inv_sa);
+    });
+  }
+  auto frag = [&](const uint8_t* tile, int row) {
+    const uint4 lo = *reinterpret_cast<const uint4*>(tile + row * F8_BK + (kg ^ (row & 7)) * 16);
+    const uint4 hi = *reinterpret_cast<const uint4*>(tile + row * F8_BK + ((kg + 4) ^ (row & 7)) * 16);
+    return i32x8_t{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+  };
+  int slot = 0;
+  for (int ct = first; ct < last; ++ct) {
+    const int n0 = ct * TL::BN + wn * TL::TN + kg * 4;
+    f32x4_t acc[TL::FM][TL::FN];
+    typename Epi::Pre pre[TL::FM][TL::FN];
+    static_for<TL::FM>([&](auto i) {
+      static_for<TL::FN>([&](auto j) {
+        acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        pre[i][j] = epi.pre(min(m0 + wm * TL::TM + i * 16 + l16, M - 1), n0 + j * 16);
+      });
+    });
+    for (int kb = 0; kb < nk; ++kb) {
+      lds_barrier();
+      i32x8_t af[TL::FM], wf[TL::FN];
+      static_for<TL::FM>([&](auto i) { af[i] = frag(As + kb * TL::BM * F8_BK, wm * TL::TM + i * 16 + l16); });
+      static_for<TL::FN>([&](auto j) { wf[j] = frag(Ws + slot * TL::STAGE, wn * TL::TN + j * 16 + l16); });
+      slot = slot == TL::ST - 1 ? 0 : slot + 1;
+      fp8_group_begin();
+      static_for<TL::FM>([&](auto i) {
+        static_for<TL::FN>([&](auto j) { acc[i][j] = mfma_fp8(wf[j], af[i], acc[i][j]); });
+      });
+      fp8_group_end();
+    }
+    static_for<TL::FM>([&](auto i) {
+      int m = m0 + wm * TL::TM + i * 16 + l16;
+      asm volatile("" : "+v"(m));  // destinations are computed here, not kept over the k loop
+      if (m < M) static_for<TL::FN>([&](auto j) { epi(m, n0 + j * 16, acc[i][j], sa, pre[i][j]); });
+    });
+  }
+  epi.finish();
+}
+
+// The row kernel while its A rows and ring fit the LDS: two blocks of 4 + 1 wavefronts per CU to
+// K = 512 (both have their fifth wavefront on the same SIMD, so 128 registers), then, and for
+// the residual epilogue, which needs more registers, blocks of 8 + 1.  The column tiles are shared by as many blocks as it takes to have one
+// round of them (a row count known only on the device is taken as 0.4 of its bound).
+template <class Epi>
+static void gemm_fp8(const bf16* A, const int32_t* m_dev, int m_max, int K, int Nout, const uint8_t* W,
+                     const float* amax_a, const Epi& epi, hipStream_t s, const int32_t* tiles = nullptr,
+                     const int32_t* ntiles = nullptr, const uint8_t* flag = nullptr) {
   if (m_max <= 0) return;
+  const size_t lds = (size_t)64 * K + (size_t)F8Rows<4>::ST * F8Rows<4>::STAGE;
+  const int mt = (m_max + 63) / 64;
+  auto rows = [&](auto nw, int slots) {
+    constexpr int NW = decltype(nw)::value;
+    static size_t granted = 0;
+    if (lds > granted) {
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_fp8_rows_kernel<NW, Epi>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      granted = lds;
+    }
+    const int expect = std::max(1, m_dev ? 2 * mt / 5 : mt);
+    const int split = std::min(std::max(slots / expect, 1), Nout / 128);
+    gemm_fp8_rows_kernel<NW, Epi><<<dim3(mt, split), 64 * NW + 64, lds, s>>>(A, m_dev, m_max, K, Nout, W, amax_a, tiles,
+                                                                        ntiles, flag, epi);
+  };
+  if constexpr (!Epi::WIDE)
+    if (K <= 512) return rows(std::integral_constant<int, 4>(), 512);
+  if (lds <= 160 * 1024) return rows(std::integral_constant<int, 8>(), 256);
+  using TL = F8Small;
   static bool attr = false;
   if (!attr) {
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_fp8_kernel<TL, Epi>),
@@ -353,30 +504,32 @@ static void gemm_fp8_launch(const bf16* A, const int32_t* m_dev, int m_max, int 
     attr = true;
   }
   dim3 grid((m_max + TL::BM - 1) / TL::BM, Nout / TL::BN);
-  gemm_fp8_kernel<TL, Epi><<<grid, TL::THREADS, TL::LDS_BYTES, s>>>(A, m_dev, m_max, K, W, amax_a, tiles, ntiles, epi);
+  gemm_fp8_kernel<TL, Epi><<<grid, TL::THREADS, TL::LDS_BYTES, s>>>(A, m_dev, m_max, K, W, amax_a, epi);
 }
-
-// Row count from which the first MLP linear uses the 8-wavefront FP8 tile (as for BF16).
-constexpr int F8_BIG_M = 32768;
 
 // x[res_rows[m], n] += s_a s_w Y + bias[n]
 struct F8ResidEpi {
+  static constexpr bool WIDE = true;
   const float* bias;
   const float* s_w;  // device: the weight's scale
   float* x;
   const int32_t* res_rows;
   int Nout;
-  __device__ __forceinline__ int need(int, int) const { return 1; }
-  __device__ __forceinline__ int list(int) const { return 0; }
-  using Pre = float4;  // x[res_rows[m], n .. n + 3]
+  __device__ __forceinline__ int skip() const { return 0; }
+  struct Pre {
+    float4 x, b4;  // x[res_rows[m], n .. n + 3]
+    int row;
+    float sw;
+  };
   __device__ __forceinline__ Pre pre(int m, int n) const {
-    return *reinterpret_cast<const float4*>(x + (size_t)res_rows[m] * Nout + n);
+    const int row = res_rows[m];
+    return {*reinterpret_cast<const float4*>(x + (size_t)row * Nout + n), *reinterpret_cast<const float4*>(bias + n), row, *s_w};
   }
-  __device__ __forceinline__ void operator()(int m, int n, const f32x4_t& a, float sa, const Pre& xin) const {
-    const float sc = sa * *s_w;
-    const float4 b4 = *reinterpret_cast<const float4*>(bias + n);
-    float4* p = reinterpret_cast<float4*>(x + (size_t)res_rows[m] * Nout + n);
-    float4 xv = xin;
+  __device__ __forceinline__ void operator()(int m, int n, const f32x4_t& a, float sa, const Pre& pr) const {
+    const float sc = sa * pr.sw;
+    const float4 b4 = pr.b4;
+    float4* p = reinterpret_cast<float4*>(x + (size_t)pr.row * Nout + n);
+    float4 xv = pr.x;
     xv.x += a[0] * sc + b4.x;
     xv.y += a[1] * sc + b4.y;
     xv.z += a[2] * sc + b4.z;
@@ -389,33 +542,31 @@ struct F8ResidEpi {
 void launch_gemm_fp8_resid(const bf16* A, const int32_t* m_dev, int m_max, int K, const uint8_t* W, const float* s_w,
                            const float* amax_a, const float* bias, int Nout, float* x, const int32_t* res_rows,
                            hipStream_t s) {
-  // (a 128 x 128 tile on 8 wavefronts measured slower here at 720p)
-  gemm_fp8_launch<F8Small>(A, m_dev, m_max, K, Nout, W, amax_a, F8ResidEpi{bias, s_w, x, res_rows, Nout}, s);
+  gemm_fp8(A, m_dev, m_max, K, Nout, W, amax_a, F8ResidEpi{bias, s_w, x, res_rows, Nout}, s);
 }
 
 // Q rows [N][C] multiplied by qscale (log2(e)/sqrt(dh): the attention kernel takes Q scaled
 // for base-2 exponentials), K [win][head][Spad][dh], V transposed [win][head][dh][spv] -- the
-// layouts of the BF16 path, so both precisions share one attention kernel.  Q tiles run over
-// the listed row tiles with a query, K/V tiles over those touching a window with queries.
+// layouts of the BF16 path, so both precisions share one attention kernel.  K/V run over the
+// listed row tiles touching a window with queries, Q over those holding one.
 struct F8QkvEpi {
+  static constexpr bool WIDE = false;
   const float* bias;
   const float* wscale;  // [0] s_q, [1] s_k, [2] s_v
   float qscale;
   bf16 *q, *k, *vt;
   int C, dh, heads, Spad, S, spv;
-  __device__ __forceinline__ int need(int, int) const { return 1; }
-  __device__ __forceinline__ int list(int n0) const { return n0 < C ? 0 : 1; }
-  struct Pre {  // the bias of the fragment's channels and the token's window and slot
+  __device__ __forceinline__ int skip() const { return C; }  // columns of a row tile without queries
+  struct Pre {  // the bias of the fragment's channels, the weight's scale
     float4 b4;
-    int w, s;
+    float sw;
   };
-  __device__ __forceinline__ Pre pre(int m, int n) const {
-    const int w = m / S;
-    return {*reinterpret_cast<const float4*>(bias + n), w, m - w * S};
+  __device__ __forceinline__ Pre pre(int, int n) const {
+    return {*reinterpret_cast<const float4*>(bias + n), wscale[n < C ? 0 : (n < 2 * C ? 1 : 2)]};
   }
   __device__ __forceinline__ void operator()(int m, int n, const f32x4_t& a, float sa, const Pre& pr) const {
     const int part = n < C ? 0 : (n < 2 * C ? 1 : 2);
-    const float sc = sa * wscale[part];
+    const float sc = sa * pr.sw;
     const float4 b4 = pr.b4;
     const float y0 = a[0] * sc + b4.x, y1 = a[1] * sc + b4.y, y2 = a[2] * sc + b4.z, y3 = a[3] * sc + b4.w;
     if (part == 0) {
@@ -426,7 +577,7 @@ struct F8QkvEpi {
       return;
     }
     const int c = n - part * C, hh = c / dh, d = c - hh * dh;
-    const int w = pr.w, s = pr.s;
+    const int w = m / S, s = m - w * S;
     if (part == 1) {
       uint2 pk;
       pk.x = pack_bf2(y0, y1);
@@ -445,26 +596,30 @@ struct F8QkvEpi {
 
 void launch_qkv_fp8(const Geo& g, int C, int heads, int Spad, int spv, const bf16* u, const int32_t* tiles,
                     const int32_t* ntiles, const uint8_t* w, const float* wscale, const float* bias,
-                    const float* amax_u, float qscale, bf16* q, bf16* k, bf16* vt, hipStream_t s) {
+                    const float* amax_u, float qscale, const uint8_t* flag, bf16* q, bf16* k, bf16* vt,
+                    hipStream_t s) {
   const F8QkvEpi epi{bias, wscale, qscale, q, k, vt, C, C / heads, heads, Spad, g.S, spv};
-  gemm_fp8_launch<F8Small>(u, nullptr, g.N, C, 3 * C, w, amax_u, epi, s, tiles, ntiles);
+  gemm_fp8(u, nullptr, g.N, C, 3 * C, w, amax_u, epi, s, tiles, ntiles, flag);
 }
 
 // h = GELU(s_a s_w Y + b1) in bf16, amax |h| of the call into *amax_h (one atomic per wave)
 struct F8GeluEpi {
+  static constexpr bool WIDE = false;
   const float* bias;
   const float* s_w;  // device: the weight's scale
   bf16* h;
   float* amax_h;
   int R;
   float mx;
-  __device__ __forceinline__ int need(int, int) const { return 1; }
-  __device__ __forceinline__ int list(int) const { return 0; }
-  struct Pre {};
-  __device__ __forceinline__ Pre pre(int, int) const { return {}; }
-  __device__ __forceinline__ void operator()(int m, int n, const f32x4_t& a, float sa, const Pre&) {
-    const float sc = sa * *s_w;
-    const float4 b4 = *reinterpret_cast<const float4*>(bias + n);
+  __device__ __forceinline__ int skip() const { return 0; }
+  struct Pre {
+    float4 b4;
+    float sw;
+  };
+  __device__ __forceinline__ Pre pre(int, int n) const { return {*reinterpret_cast<const float4*>(bias + n), *s_w}; }
+  __device__ __forceinline__ void operator()(int m, int n, const f32x4_t& a, float sa, const Pre& pr) {
+    const float sc = sa * pr.sw;
+    const float4 b4 = pr.b4;
     const float y0 = gelu_fast(a[0] * sc + b4.x), y1 = gelu_fast(a[1] * sc + b4.y);
     const float y2 = gelu_fast(a[2] * sc + b4.z), y3 = gelu_fast(a[3] * sc + b4.w);
     mx = fmaxf(mx, fmaxf(fmaxf(fabsf(y0), fabsf(y1)), fmaxf(fabsf(y2), fabsf(y3))));
@@ -482,10 +637,7 @@ struct F8GeluEpi {
 void launch_fc1_fp8(int m_max, const int32_t* m_dev, int C, int R, const bf16* u, const uint8_t* w, const float* s_w,
                     const float* bias, const float* amax_u, bf16* h, float* amax_h, hipStream_t s) {
   const F8GeluEpi epi{bias, s_w, h, amax_h, R, 0.f};
-  if (m_max >= F8_BIG_M && R % 256 == 0)
-    gemm_fp8_launch<F8Tile<128, 256, 2, 4>>(u, m_dev, m_max, C, R, w, amax_u, epi, s);
-  else
-    gemm_fp8_launch<F8Small>(u, m_dev, m_max, C, R, w, amax_u, epi, s);
+  gemm_fp8(u, m_dev, m_max, C, R, w, amax_u, epi, s);
 }
 
 bool fp8_supported(int C, int R) { return C % 128 == 0 && R % 128 == 0 && C / 64 <= LNR_PER_MAX; }

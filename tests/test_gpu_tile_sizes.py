@@ -1,0 +1,43 @@
+"""Results do not depend on which tile a row count selects: clips in one batch against the same
+clips one by one, bit for bit, and the FP8 products at every way their rows are held."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import drsynth
+from oracle import network as on
+from tests.gpu_util import MID, TOL, compare
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("precision", ["bf16", "fp8"])
+@pytest.mark.parametrize("net", ["clip240", "clip240_dec", "clip720"])
+def test_batch_and_single_clips_agree_bitwise(net, precision):
+    """Two or three clips exceed 32k tokens (two row tiles per block, several tiles per block),
+    one does not; listed row tiles are odd in number for some of them.  In FP8 the activation
+    scales are the call's, so the clips of a batch are copies of one clip."""
+    from paper_2509_10466_amd import Inpainter
+    cfg = dataclasses.replace(drsynth.NETS[net], blocks=2)
+    H, W = (240, 432) if cfg.win_h == 5 else (240, 400)
+    eng = Inpainter(cfg, drsynth.make_weights(cfg, 1))
+    for n in (2, 3):
+        f, m = drsynth.make_clip_batch([4] * n if precision == "fp8" else range(4, 4 + n), 5, H, W)
+        f, m = torch.from_numpy(f).cuda(), torch.from_numpy(m).cuda()
+        whole = eng(f, m, precision)
+        for b in range(n):
+            assert torch.equal(eng(f[b:b + 1].contiguous(), m[b:b + 1].contiguous(), precision)[0], whole[b])
+
+
+@pytest.mark.parametrize("dim,ratio", [(128, 4), (256, 5), (384, 4), (512, 4)])
+def test_fp8_row_lengths(dim, ratio):
+    """Rows of 128 to 2048 values: held in LDS by 4 or 8 wavefronts, or (2048) too long for it."""
+    from paper_2509_10466_amd import Inpainter
+    cfg = dataclasses.replace(MID, dim=dim, heads=dim // 64, mlp_ratio=ratio)
+    W = drsynth.make_weights(cfg, 2)
+    f, m, _ = drsynth.make_clip(5, 5, 40, 72, cov_range=(0.2, 0.4))
+    out = Inpainter(cfg, W)(torch.from_numpy(f).cuda(), torch.from_numpy(m).cuda(), "fp8").cpu().numpy()
+    compare(out, on.forward(f, m, W, cfg), f, m, TOL["fp8"])
+    assert np.isfinite(out).all()
