@@ -10,53 +10,62 @@ namespace dr {
 // LayerNorm over C channels, biased variance, eps = 1e-5; one wavefront per row.
 // Input row r is x[rows ? rows[r] : r]; output row r is compact.
 // ------------------------------------------------------------------------------------------
-template <typename OutT>
-__device__ __forceinline__ void store_val(OutT* p, float v);
-template <>
-__device__ __forceinline__ void store_val<float>(float* p, float v) { *p = v; }
-template <>
-__device__ __forceinline__ void store_val<bf16>(bf16* p, float v) { *p = f2bf(v); }
-
-template <typename OutT>
+// PER = C / 64 values per lane, fixed at compile time for the network widths, so that a row's
+// loads are issued together.  `copy` (if given) receives the row as read.
+template <int PER>
 __global__ void __launch_bounds__(256) ln_kernel(const float* __restrict__ x, const int32_t* __restrict__ rows,
                                                  const int32_t* __restrict__ nrows_dev, int nrows_max, int C,
                                                  const float* __restrict__ g, const float* __restrict__ b,
-                                                 OutT* __restrict__ y, float* __restrict__ copy) {
+                                                 float* __restrict__ y, float* __restrict__ copy) {
   const int lane = threadIdx.x & 63;
   const int r = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int nrows = nrows_dev ? nrows_dev[0] : nrows_max;
   if (r >= nrows) return;
   const int src = rows ? rows[r] : r;
   const float* xr = x + (size_t)src * C;
-  const int per = C / 64;
-  float v[16];
+  constexpr int MAXP = PER ? PER : 16;
+  const int per = PER ? PER : C / 64;
+  float v[MAXP];
   float s = 0.f;
-  for (int e = 0; e < per; ++e) {
-    v[e] = xr[lane + 64 * e];
-    s += v[e];
-  }
-  if (copy)
-    for (int e = 0; e < per; ++e) copy[(size_t)r * C + lane + 64 * e] = v[e];
+#pragma unroll
+  for (int e = 0; e < MAXP; ++e)
+    if (e < per) v[e] = xr[lane + 64 * e];
+#pragma unroll
+  for (int e = 0; e < MAXP; ++e)
+    if (e < per) {
+      s += v[e];
+      if (copy) copy[(size_t)r * C + lane + 64 * e] = v[e];
+    }
   const float mean = wave_sum(s) / C;
   float q = 0.f;
-  for (int e = 0; e < per; ++e) {
-    const float d = v[e] - mean;
-    q += d * d;
-  }
+#pragma unroll
+  for (int e = 0; e < MAXP; ++e)
+    if (e < per) {
+      const float d = v[e] - mean;
+      q = fmaf(d, d, q);
+    }
   const float rstd = rsqrtf(wave_sum(q) / C + 1e-5f);
-  OutT* yr = y + (size_t)r * C;
-  for (int e = 0; e < per; ++e) {
-    const int c = lane + 64 * e;
-    store_val<OutT>(yr + c, (v[e] - mean) * rstd * g[c] + b[c]);
-  }
+  float* yr = y + (size_t)r * C;
+#pragma unroll
+  for (int e = 0; e < MAXP; ++e)
+    if (e < per) {
+      const int c = lane + 64 * e;
+      yr[c] = fmaf((v[e] - mean) * rstd, g[c], b[c]);
+    }
 }
 
 void launch_ln_f32(const float* x, const int32_t* rows, const int32_t* nrows_dev, int nrows_max,
                    int C, const float* g, const float* b, float* y, hipStream_t s, float* copy) {
   if (nrows_max <= 0) return;
-  ln_kernel<float><<<(nrows_max + 3) / 4, 256, 0, s>>>(x, rows, nrows_dev, nrows_max, C, g, b, y, copy);
+  const int grid = (nrows_max + 3) / 4;
+  switch (C) {
+    case 64: ln_kernel<1><<<grid, 256, 0, s>>>(x, rows, nrows_dev, nrows_max, C, g, b, y, copy); break;
+    case 128: ln_kernel<2><<<grid, 256, 0, s>>>(x, rows, nrows_dev, nrows_max, C, g, b, y, copy); break;
+    case 256: ln_kernel<4><<<grid, 256, 0, s>>>(x, rows, nrows_dev, nrows_max, C, g, b, y, copy); break;
+    case 384: ln_kernel<6><<<grid, 256, 0, s>>>(x, rows, nrows_dev, nrows_max, C, g, b, y, copy); break;
+    default: ln_kernel<0><<<grid, 256, 0, s>>>(x, rows, nrows_dev, nrows_max, C, g, b, y, copy); break;
+  }
 }
-
 
 // ------------------------------------------------------------------------------------------
 // Window attention, FP32: one wavefront per (window, head, query).  Scores over all S keys of

@@ -5,6 +5,8 @@
 // "Inpainting Manager"); the output keeps every non-private pixel of the input and takes
 // generated content only inside the mask.  Both steps are FP32 in every precision mode:
 // together they are well under 1 % of the path's arithmetic.
+#include <algorithm>
+
 #include "dr_device.h"
 #include "dr_internal.h"
 #include "gemm_core.h"
@@ -96,11 +98,16 @@ void launch_embed(const Geo& g, int C, const float* frames, const uint8_t* masks
 
 // ------------------------------------------------------------------------------------------
 // Final LayerNorm + decoder + sigmoid, then the masked pixels of each flagged token are
-// written.  One wavefront per flagged token; the decoder matrix [C][48] lives in LDS.
+// written; the decoder matrix [C][48] lives in LDS.
 // ------------------------------------------------------------------------------------------
-constexpr int DEC_GRID = 1024;
 
-__global__ void __launch_bounds__(256) decode_kernel(Geo g, int C, const float* __restrict__ x,
+// A wavefront takes TW tokens at a time: a weight value read from LDS serves all of them, and a
+// token's z values come four channels per read (one token at a time, two LDS reads per fused
+// multiply-add: 448 us at 84,000 tokens of 384).  Each output is one chain of fused multiply-adds
+// over the channels in order.
+constexpr int DEC_GRID = 1024;
+template <int NWV, int TW, int PER>
+__global__ void __launch_bounds__(64 * NWV) decode_kernel(Geo g, int C, const float* __restrict__ x,
                                                      const int32_t* __restrict__ idx,
                                                      const int32_t* __restrict__ nq,
                                                      const float* __restrict__ lng,
@@ -109,64 +116,113 @@ __global__ void __launch_bounds__(256) decode_kernel(Geo g, int C, const float* 
                                                      const float* __restrict__ db,
                                                      const uint8_t* __restrict__ masks,
                                                      float* __restrict__ out) {
-  extern __shared__ float sm[];
+  extern __shared__ __align__(16) float sm[];
   float* Wd = sm;                      // [C][48]
-  float* Z = sm + (size_t)C * 48;      // [4][C]
+  float* Z = sm + (size_t)C * 48;      // [NWV][TW][C]
+  const int total = nq[0];
+  if ((int)blockIdx.x * NWV * TW >= total) return;  // uniform per block
   for (int e = threadIdx.x; e < C * 48; e += blockDim.x) Wd[e] = dw[e];
   __syncthreads();
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  float* z = Z + wv * C;
-  const int total = nq[0];
-  const int per = C / 64;
-  for (int r = blockIdx.x * 4 + wv; r < total; r += gridDim.x * 4) {
-    const int n = idx[r];
-    const float* xr = x + (size_t)n * C;
-    float v[16];
-    float s = 0.f;
-    for (int e = 0; e < per; ++e) {
-      v[e] = xr[lane + 64 * e];
-      s += v[e];
+  float* z = Z + (size_t)wv * TW * C;
+  constexpr int MAXP = PER ? PER : 16;
+  const int per = PER ? PER : C / 64;
+  for (int r0 = (blockIdx.x * NWV + wv) * TW; r0 < total; r0 += gridDim.x * NWV * TW) {
+    // (the row length is fixed at compile time for the network widths, so that the rows' loads
+    // are issued together)
+    float v[TW][MAXP];
+#pragma unroll
+    for (int u = 0; u < TW; ++u) {
+      const float* xr = x + (size_t)idx[min(r0 + u, total - 1)] * C;
+#pragma unroll
+      for (int e = 0; e < MAXP; ++e)
+        if (e < per) v[u][e] = xr[lane + 64 * e];
     }
-    const float mean = wave_sum(s) / C;
-    float q = 0.f;
-    for (int e = 0; e < per; ++e) {
-      const float d = v[e] - mean;
-      q += d * d;
-    }
-    const float rstd = rsqrtf(wave_sum(q) / C + 1e-5f);
-    for (int e = 0; e < per; ++e) {
-      const int c = lane + 64 * e;
-      z[c] = (v[e] - mean) * rstd * lng[c] + lnb[c];
+#pragma unroll
+    for (int u = 0; u < TW; ++u) {
+      float s = 0.f;
+#pragma unroll
+      for (int e = 0; e < MAXP; ++e)
+        if (e < per) s += v[u][e];
+      const float mean = wave_sum(s) / C;
+      float q = 0.f;
+#pragma unroll
+      for (int e = 0; e < MAXP; ++e)
+        if (e < per) {
+          const float d = v[u][e] - mean;
+          q = fmaf(d, d, q);
+        }
+      const float rstd = rsqrtf(wave_sum(q) / C + 1e-5f);
+#pragma unroll
+      for (int e = 0; e < MAXP; ++e)
+        if (e < per) {
+          const int c = lane + 64 * e;
+          z[u * C + c] = fmaf((v[u][e] - mean) * rstd, lng[c], lnb[c]);
+        }
     }
     __builtin_amdgcn_wave_barrier();
     if (lane < 48) {
-      float acc = db[lane % 3];
-      for (int c = 0; c < C; ++c) acc = fmaf(z[c], Wd[c * 48 + lane], acc);
-      const float pred = 1.0f / (1.0f + expf(-acc));
-      int b, t, i, j;
-      token_coords(g, n, b, t, i, j);
+      float acc[TW];
+#pragma unroll
+      for (int u = 0; u < TW; ++u) acc[u] = db[lane % 3];
+      for (int c = 0; c < C; c += 4) {
+        float w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = Wd[(c + e) * 48 + lane];
+#pragma unroll
+        for (int u = 0; u < TW; ++u) {
+          const float4 zv = *reinterpret_cast<const float4*>(z + u * C + c);
+          acc[u] = fmaf(zv.x, w[0], acc[u]);
+          acc[u] = fmaf(zv.y, w[1], acc[u]);
+          acc[u] = fmaf(zv.z, w[2], acc[u]);
+          acc[u] = fmaf(zv.w, w[3], acc[u]);
+        }
+      }
       const int pix = lane / 3, ch = lane - 3 * pix;
       const int ky = pix >> 2, kx = pix & 3;
-      const size_t px = (((size_t)b * g.T + t) * g.H + 4 * i + ky) * g.W + 4 * j + kx;
-      if (masks[px]) out[px * 3 + ch] = pred;
+#pragma unroll
+      for (int u = 0; u < TW; ++u) {
+        if (r0 + u < total) {
+          const float pred = 1.0f / (1.0f + expf(-acc[u]));
+          int b, t, i, j;
+          token_coords(g, idx[r0 + u], b, t, i, j);
+          const size_t px = (((size_t)b * g.T + t) * g.H + 4 * i + ky) * g.W + 4 * j + kx;
+          if (masks[px]) out[px * 3 + ch] = pred;
+        }
+      }
     }
     __builtin_amdgcn_wave_barrier();
   }
 }
 
-void launch_decode(const Geo& g, int C, const float* x, const int32_t* idx, const int32_t* nq,
-                   const float* lng, const float* lnb, const float* dw, const float* db,
-                   const uint8_t* masks, float* out, hipStream_t s) {
-  const size_t smem = (size_t)C * 48 * sizeof(float) + 4 * (size_t)C * sizeof(float);
-  int grid = (g.N + 3) / 4;
-  if (grid > DEC_GRID) grid = DEC_GRID;
+template <int NWV, int TW, int PER>
+static void decode_launch(const Geo& g, int C, const float* x, const int32_t* idx, const int32_t* nq, const float* lng,
+                          const float* lnb, const float* dw, const float* db, const uint8_t* masks, float* out,
+                          hipStream_t s) {
+  const size_t smem = (size_t)C * (48 + NWV * TW) * sizeof(float);
   static size_t granted = 0;
-  if (smem > 65536 && smem > granted) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(decode_kernel),
+  if (smem > granted) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(decode_kernel<NWV, TW, PER>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     granted = smem;
   }
-  decode_kernel<<<grid, 256, smem, s>>>(g, C, x, idx, nq, lng, lnb, dw, db, masks, out);
+  // eight wavefronts' rows leave room for one block per CU, which then stages the weight once
+  const int grid = std::min((g.N + NWV * TW - 1) / (NWV * TW), NWV == 8 ? 256 : DEC_GRID);
+  decode_kernel<NWV, TW, PER><<<grid, 64 * NWV, smem, s>>>(g, C, x, idx, nq, lng, lnb, dw, db, masks, out);
+}
+
+void launch_decode(const Geo& g, int C, const float* x, const int32_t* idx, const int32_t* nq,
+                   const float* lng, const float* lnb, const float* dw, const float* db,
+                   const uint8_t* masks, float* out, hipStream_t s) {
+  // the weight and 8 x 4 tokens' rows fit the LDS up to 512 channels
+  auto run = [&](auto launch) { launch(g, C, x, idx, nq, lng, lnb, dw, db, masks, out, s); };
+  switch (C) {
+    case 64: return run(decode_launch<8, 4, 1>);
+    case 128: return run(decode_launch<8, 4, 2>);
+    case 256: return run(decode_launch<8, 4, 4>);
+    case 384: return run(decode_launch<8, 4, 6>);
+    default: return run(C <= 512 ? decode_launch<8, 4, 0> : decode_launch<4, 1, 0>);
+  }
 }
 
 // ------------------------------------------------------------------------------------------
