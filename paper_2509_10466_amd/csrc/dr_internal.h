@@ -264,9 +264,10 @@ void launch_attn_train_fwd(const Geo& g, int C, int heads, const float* q, const
                            float* o, float2* stats, hipStream_t s);
 
 // Token reductions of the training passes: rows per partial
-constexpr int TN_CHUNK = 2048;  // weight gradients and column sums
+constexpr int TN_CHUNK = 2048;  // column sums, and weight gradients with bf16 operands
+inline int tn_chunk(bool bf16) { return bf16 ? TN_CHUNK : TN_CHUNK / 2; }  // weight gradients
 constexpr int LNB_ROWS = 64;    // LayerNorm gain and shift gradients
-inline int tn_chunks(int M_max) { return (M_max + TN_CHUNK - 1) / TN_CHUNK; }
+inline int tn_chunks(int M_max, int chunk = TN_CHUNK) { return (M_max + chunk - 1) / chunk; }
 inline int ln_bwd_blocks(int n_max) { return (n_max + LNB_ROWS - 1) / LNB_ROWS; }
 
 // FP8 path (OCP e4m3 operands, per-tensor scales s = amax/448, FP32 accumulation)

@@ -31,10 +31,8 @@ void launch_ln_bwd(const float* x, const int32_t* n_dev, int n_max, int C, const
                    const float* acc, float* dx, float* part, hipStream_t s);
 void launch_sum_parts(const float* part, int nparts, size_t stride, const int32_t* n_dev, int rows_per, int width,
                       float* out, hipStream_t s);
-void launch_tn_f32(const float* A, const int32_t* arow, int lda, const float* B, const int32_t* brow, int ldb,
-                       const int32_t* M_dev, int M_max, int I, int J, float* part, hipStream_t s);
-void launch_tn_bf16ops(const float* A, const int32_t* arow, int lda, const float* B, const int32_t* brow, int ldb,
-                       const int32_t* M_dev, int M_max, int I, int J, float* part, hipStream_t s);
+void launch_tn(bool bf16, const float* A, int lda, const float* B, const int32_t* brow, int ldb, const int32_t* M_dev,
+               int M_max, int I, int J, float* part, hipStream_t s);
 void launch_colsum_partial(const float* B, int ldb, const int32_t* M_dev, int M_max, int J, float* part, hipStream_t s);
 void launch_patches(const Geo& g, const float* frames, const uint8_t* masks, float* P, hipStream_t s);
 void launch_decoder_full(const Geo& g, int C, const float* z, const float* dw, const float* db, float* pred, hipStream_t s);
@@ -177,7 +175,7 @@ static dr_status scratch_reserve(dr_ctx* c, dr_train* t, const Geo& g) {
     t->dsum = (float*)A(N * H * 4);
     t->dyt = (float*)A(N * 48 * 4);
     t->dz = (float*)A(N * C * 4);
-    t->part = (float*)A((size_t)tn_chunks((int)N) * std::max(R, 2 * C) * C * 4);
+    t->part = (float*)A((size_t)tn_chunks((int)N, tn_chunk(false)) * std::max(R, 2 * C) * C * 4);
     t->lnpart = (float*)A((size_t)ln_bwd_blocks((int)N) * 2 * C * 4);
     t->zeros = (float*)A((2 * C + R + 64) * 4);
     t->tmp = (float*)A((R * C + 64) * 4);
@@ -379,10 +377,10 @@ extern "C" dr_status dr_saved_free(dr_ctx* c, dr_saved* sv) {
 }
 
 // grads[off .. off + I*J) = sum over chunks of TN partials
-static void tn_grad(dr_train* t, bool bf16, const float* A, const int32_t* arow, int lda, const float* Bm, const int32_t* brow,
-                    int ldb, const int32_t* M_dev, int M_max, int I, int J, float* out, hipStream_t s) {
-  (bf16 ? launch_tn_bf16ops : launch_tn_f32)(A, arow, lda, Bm, brow, ldb, M_dev, M_max, I, J, t->part, s);
-  launch_sum_parts(t->part, tn_chunks(M_max), (size_t)I * J, M_dev, TN_CHUNK, I * J, out, s);
+static void tn_grad(dr_train* t, bool bf16, const float* A, int lda, const float* Bm, const int32_t* brow, int ldb,
+                    const int32_t* M_dev, int M_max, int I, int J, float* out, hipStream_t s) {
+  launch_tn(bf16, A, lda, Bm, brow, ldb, M_dev, M_max, I, J, t->part, s);
+  launch_sum_parts(t->part, tn_chunks(M_max, tn_chunk(bf16)), (size_t)I * J, M_dev, tn_chunk(bf16), I * J, out, s);
 }
 
 static void colsum_grad(dr_train* t, const float* Bm, int ldb, const int32_t* M_dev, int M_max, int J, float* out,
@@ -436,7 +434,7 @@ extern "C" dr_status dr_train_backward(dr_ctx* c, dr_saved* sv, const float* dpr
   float* G = grads;
   // decoder: dyt = dpred * pred (1 - pred) per token and (ky, kx, ch)
   launch_dec_grad_tok(g, sv->pred, dpred, t->dyt, s);
-  tn_grad(t, b16, sv->z, nullptr, C, t->dyt, nullptr, 48, nullptr, N, C, 48, t->tmp, s);
+  tn_grad(t, b16, sv->z, C, t->dyt, nullptr, 48, nullptr, N, C, 48, t->tmp, s);
   permute48_kernel<<<(C * 48 + 255) / 256, 256, 0, s>>>(t->tmp, C, G + po.dw);
   colsum_grad(t, t->dyt, 48, nullptr, N, 48, t->tmp, s);
   fold48_kernel<<<1, 64, 0, s>>>(t->tmp, G + po.db);
@@ -454,15 +452,15 @@ extern "C" dr_status dr_train_backward(dr_ctx* c, dr_saved* sv, const float* dpr
     // dh = (dx2 W2) GELU'(hpre) and GELU(hpre) again
     train_gemm(b16, t->dx2, nullptr, sv->nq, N, C, W(b.w2T), t->zeros, R, EPI_STORE, t->dh, nullptr, s);
     launch_gelu_bwd(tb.hpre, sv->nq, N, R, t->dh, t->a, s);
-    tn_grad(t, b16, t->dx2, nullptr, C, t->a, nullptr, R, sv->nq, N, C, R, G + pb.w2, s);
+    tn_grad(t, b16, t->dx2, C, t->a, nullptr, R, sv->nq, N, C, R, G + pb.w2, s);
     colsum_grad(t, t->dx2, C, sv->nq, N, C, G + pb.b2, s);
-    tn_grad(t, b16, t->dh, nullptr, R, tb.n2, nullptr, C, sv->nq, N, R, C, G + pb.w1, s);
+    tn_grad(t, b16, t->dh, R, tb.n2, nullptr, C, sv->nq, N, R, C, G + pb.w1, s);
     colsum_grad(t, t->dh, R, sv->nq, N, R, G + pb.b1, s);
     train_gemm(b16, t->dh, nullptr, sv->nq, N, R, W(b.w1T), t->zeros, C, EPI_STORE, t->dn2, nullptr, s);
     launch_ln_bwd(tb.x1, sv->nq, N, C, W(b.ln2g), t->dn2, t->dx2, t->dx1, t->lnpart, s);
     launch_sum_parts(t->lnpart, ln_bwd_blocks(N), 2 * C, sv->nq, LNB_ROWS, 2 * C, G + pb.ln2g, s);  // ln2.g then ln2.b
     // x1 = x + Wo O + bo
-    tn_grad(t, b16, t->dx1, nullptr, C, tb.o, nullptr, C, sv->nq, N, C, C, G + pb.wo, s);
+    tn_grad(t, b16, t->dx1, C, tb.o, nullptr, C, sv->nq, N, C, C, G + pb.wo, s);
     colsum_grad(t, t->dx1, C, sv->nq, N, C, G + pb.bo, s);
     train_gemm(b16, t->dx1, nullptr, sv->nq, N, C, W(b.woT), t->zeros, C, EPI_STORE, t->dout, nullptr, s);
     launch_scatter_rows(t->dx1, sv->idx, sv->nq, N, C, t->dx, s);
@@ -472,12 +470,13 @@ extern "C" dr_status dr_train_backward(dr_ctx* c, dr_saved* sv, const float* dpr
     launch_attn_train_dkv(g, C, heads, tb.q, tb.kv, t->dout, tb.stats, t->dsum, sv->woff, t->dkv, s);
     KCHECK("attention backward");
     // Q, K, V projections
-    tn_grad(t, b16, t->dq, nullptr, C, tb.u, sv->idx, C, sv->nq, N, C, C, G + pb.wq, s);
+    tn_grad(t, b16, t->dq, C, tb.u, sv->idx, C, sv->nq, N, C, C, G + pb.wq, s);
     colsum_grad(t, t->dq, C, sv->nq, N, C, G + pb.bq, s);
     // W_k and W_v (and their biases) in one reduction over the same rows of u
-    (b16 ? launch_tn_bf16ops : launch_tn_f32)(t->dkv, nullptr, 2 * C, tb.u, nullptr, C, nullptr, N, 2 * C, C, t->part, s);
-    launch_sum_parts(t->part, tn_chunks(N), (size_t)2 * C * C, nullptr, TN_CHUNK, C * C, G + pb.wk, s);
-    launch_sum_parts(t->part + (size_t)C * C, tn_chunks(N), (size_t)2 * C * C, nullptr, TN_CHUNK, C * C, G + pb.wv, s);
+    launch_tn(b16, t->dkv, 2 * C, tb.u, nullptr, C, nullptr, N, 2 * C, C, t->part, s);
+    const int nch = tn_chunks(N, tn_chunk(b16));
+    launch_sum_parts(t->part, nch, (size_t)2 * C * C, nullptr, tn_chunk(b16), C * C, G + pb.wk, s);
+    launch_sum_parts(t->part + (size_t)C * C, nch, (size_t)2 * C * C, nullptr, tn_chunk(b16), C * C, G + pb.wv, s);
     launch_colsum_partial(t->dkv, 2 * C, nullptr, N, 2 * C, t->part, s);
     launch_sum_parts(t->part, tn_chunks(N), 2 * C, nullptr, TN_CHUNK, C, G + pb.bk, s);
     launch_sum_parts(t->part + C, tn_chunks(N), 2 * C, nullptr, TN_CHUNK, C, G + pb.bv, s);
@@ -489,7 +488,7 @@ extern "C" dr_status dr_train_backward(dr_ctx* c, dr_saved* sv, const float* dpr
     KCHECK("qkv backward");
   }
   // patch embedding
-  tn_grad(t, b16, t->dx, nullptr, C, sv->patches, nullptr, 48, nullptr, N, C, 48, t->tmp, s);
+  tn_grad(t, b16, t->dx, C, sv->patches, nullptr, 48, nullptr, N, C, 48, t->tmp, s);
   permute48_kernel<<<(C * 48 + 255) / 256, 256, 0, s>>>(t->tmp, C, G + po.ew);
   colsum_grad(t, t->dx, C, nullptr, N, C, G + po.eb, s);
   KCHECK("embed backward");

@@ -14,7 +14,8 @@
 //     range) is recomputed by the fused multiply-adds, so infinities come out as they do there.
 //   NP = 1 (mixed precision): operands rounded to bf16 to nearest even, one product.
 //
-// Block = 4 wavefronts (2 x 2), BM x BN outputs, k in steps of 32.  Operands are read from
+// Block = 4 wavefronts (2 x 2), BM x BN outputs, k in steps of 32.  Operands of the linears
+// (the weight gradients' are described with them) are read from
 // global memory into registers one step ahead, split there, and written to LDS as bf16 planes
 // (the split is done once per block and element, not once per wavefront); two blocks per CU
 // hide each other's barriers.  A row of 32 k values is 64 bytes, two rows share a 128-byte
@@ -41,12 +42,13 @@ __device__ __forceinline__ int ops_off(int r, int c) {
   return line * 64 + (((((r & 1) << 2) | c) ^ (line & 7)) << 3);
 }
 
-// 8 values -> their bf16 planes in LDS
-template <class TL>
-__device__ __forceinline__ void ops_put(bf16_t* lds, int off, const float (&v)[8]) {
-  if constexpr (TL::NP == 1) {
-    *reinterpret_cast<u32x4_t*>(lds + off) =
-        u32x4_t{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7])};
+// put(p, plane p of 8 values)
+template <int NP, class Put>
+__device__ __forceinline__ void ops_split(const float (&v)[8], const Put& put) {
+  using I0 = std::integral_constant<int, 0>;
+  if constexpr (NP == 1) {
+    put(I0{}, __builtin_bit_cast(bf16x8_t, u32x4_t{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]),
+                                                   pack_bf2(v[6], v[7])}));
   } else {
     u32x4_t p1, p2, p3;
     static_for<4>([&](auto h) {
@@ -57,10 +59,32 @@ __device__ __forceinline__ void ops_put(bf16_t* lds, int off, const float (&v)[8
       p2[int(h)] = q;
       p3[int(h)] = pack_bf2(ra - __uint_as_float(q << 16), rb - __uint_as_float(q & 0xffff0000u));
     });
-    *reinterpret_cast<u32x4_t*>(lds + off) = p1;
-    *reinterpret_cast<u32x4_t*>(lds + TL::PLANE + off) = p2;
-    *reinterpret_cast<u32x4_t*>(lds + 2 * TL::PLANE + off) = p3;
+    put(I0{}, __builtin_bit_cast(bf16x8_t, p1));
+    put(std::integral_constant<int, 1>{}, __builtin_bit_cast(bf16x8_t, p2));
+    put(std::integral_constant<int, 2>{}, __builtin_bit_cast(bf16x8_t, p3));
   }
+}
+
+// acc[..][j] += the products of the operand fragments af and wf (of column fragment j)
+template <class TL, class J>
+__device__ __forceinline__ void ops_products(const bf16x8_t (&af)[TL::NP][TL::FM], const bf16x8_t (&wf)[TL::NP],
+                                             f32x4_t (&acc)[TL::FM][TL::FN], J j) {
+  auto product = [&](auto pw, auto pa) {
+    static_for<TL::FM>([&](auto i) { acc[i][j] = mfma_bf16_16x16x32(wf[pw], af[pa][i], acc[i][j]); });
+  };
+  using I0 = std::integral_constant<int, 0>;
+  mfma_fence_begin();
+  if constexpr (TL::NP == 3) {
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    product(I0{}, I2{});
+    product(I1{}, I1{});
+    product(I2{}, I0{});
+    product(I0{}, I1{});
+    product(I1{}, I0{});
+  }
+  product(I0{}, I0{});
+  mfma_fence_end();
 }
 
 // acc += the tile's products over `steps` k steps.  la / lw: load(step, slot, v) reads the
@@ -68,52 +92,39 @@ __device__ __forceinline__ void ops_put(bf16_t* lds, int off, const float (&v)[8
 template <class TL, class LA, class LW>
 __device__ __forceinline__ void ops_core(const LA& la, const LW& lw, int steps, bf16_t* lds,
                                          f32x4_t (&acc)[TL::FM][TL::FN]) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int wm = wv >> 1, wn = wv & 1, l16 = lane & 15, kg = lane >> 4;
   static_for<TL::FM>([&](auto i) {
     static_for<TL::FN>([&](auto j) { acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; });
   });
   if (steps <= 0) return;  // uniform per block
-  int aoff[TL::SA], woff[TL::SW];
-  static_for<TL::SA>([&](auto s) { aoff[s] = ops_off(la.row(s), la.chunk(s)); });
-  static_for<TL::SW>([&](auto s) { woff[s] = ops_off(TL::BM + lw.row(s), lw.chunk(s)); });
-  int afrag[TL::FM], wfrag[TL::FN];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int wm = wv >> 1, wn = wv & 1, l16 = lane & 15, kg = lane >> 4;
+  int afrag[TL::FM], wfrag[TL::FN], aoff[TL::SA], woff[TL::SW];
   static_for<TL::FM>([&](auto i) { afrag[i] = ops_off(wm * 16 * TL::FM + 16 * i + l16, kg); });
   static_for<TL::FN>([&](auto j) { wfrag[j] = ops_off(TL::BM + wn * 16 * TL::FN + 16 * j + l16, kg); });
+  static_for<TL::SA>([&](auto s) { aoff[s] = ops_off(la.row(s), la.chunk(s)); });
+  static_for<TL::SW>([&](auto s) { woff[s] = ops_off(TL::BM + lw.row(s), lw.chunk(s)); });
   float va[TL::SA][8], vw[TL::SW][8];
   auto load = [&](int step) {
     static_for<TL::SA>([&](auto s) { la.load(step, s, va[s]); });
     static_for<TL::SW>([&](auto s) { lw.load(step, s, vw[s]); });
   };
+  auto put = [&](int off, const float(&v)[8]) {
+    ops_split<TL::NP>(v, [&](auto p, bf16x8_t x) { *reinterpret_cast<bf16x8_t*>(lds + p * TL::PLANE + off) = x; });
+  };
+  bf16x8_t af[TL::NP][TL::FM], wf[2][TL::NP];
+  auto get = [&](int p, int off) { return *reinterpret_cast<const bf16x8_t*>(lds + p * TL::PLANE + off); };
   load(0);
   for (int step = 0; step < steps; ++step) {
-    static_for<TL::SA>([&](auto s) { ops_put<TL>(lds, aoff[s], va[s]); });
-    static_for<TL::SW>([&](auto s) { ops_put<TL>(lds, woff[s], vw[s]); });
+    static_for<TL::SA>([&](auto s) { put(aoff[s], va[s]); });
+    static_for<TL::SW>([&](auto s) { put(woff[s], vw[s]); });
     lds_barrier();
     if (step + 1 < steps) load(step + 1);
-    bf16x8_t af[TL::NP][TL::FM], wf[2][TL::NP];
-    auto get = [&](int p, int off) { return *reinterpret_cast<const bf16x8_t*>(lds + p * TL::PLANE + off); };
     static_for<TL::NP>([&](auto p) { wf[0][p] = get(p, wfrag[0]); });
     static_for<TL::NP>([&](auto p) { static_for<TL::FM>([&](auto i) { af[p][i] = get(p, afrag[i]); }); });
     static_for<TL::FN>([&](auto j) {
       constexpr int b = j & 1;
       if constexpr (j + 1 < TL::FN) static_for<TL::NP>([&](auto p) { wf[b ^ 1][p] = get(p, wfrag[j + 1]); });
-      auto product = [&](auto pw, auto pa) {
-        static_for<TL::FM>([&](auto i) { acc[i][j] = mfma_bf16_16x16x32(wf[b][pw], af[pa][i], acc[i][j]); });
-      };
-      using I0 = std::integral_constant<int, 0>;
-      mfma_fence_begin();
-      if constexpr (TL::NP == 3) {
-        using I1 = std::integral_constant<int, 1>;
-        using I2 = std::integral_constant<int, 2>;
-        product(I0{}, I2{});
-        product(I1{}, I1{});
-        product(I2{}, I0{});
-        product(I0{}, I1{});
-        product(I1{}, I0{});
-      }
-      product(I0{}, I0{});
-      mfma_fence_end();
+      ops_products<TL>(af, wf[b], acc, j);
     });
     lds_barrier();
   }
@@ -218,6 +229,14 @@ __global__ void __launch_bounds__(TL::THREADS, 2) gemm_ops_kernel(const float* _
   });
 }
 
+// dynamic LDS beyond 64 KB has to be asked for
+template <class K>
+static void ops_allow_lds(K kernel, size_t bytes) {
+  if (bytes > 65536)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)bytes);
+}
+
 // Blocks below which the 64 x 64 tile is taken: 128 x 128 tiles run two per CU, so fewer than
 // 512 of them leave CUs idle.  A row count known only on the device (the query rows) is taken
 // as 0.4 of its bound, the most a clip's mask is expected to cover.
@@ -251,58 +270,136 @@ void launch_gemm_bf16ops(const float* A, const int32_t* arows, const int32_t* m_
 
 // ------------------------------------------------------------------------------------------
 // Token reductions (weight gradients): part[chunk][i][j] = sum over the chunk's rows m of
-// A[arow(m)][i] B[brow(m)][j], m < *M_dev (or M_max), TN_CHUNK rows per chunk, A row stride
-// lda, B row stride ldb, i < I, j < J (J % 4 == 0).  Chunks past the last row write nothing
-// (launch_sum_parts reads only the chunks in use).  The contraction runs over rows, so a
-// thread reads 8 rows of one column (a wavefront reads 64 adjacent columns of a row at a time)
-// and holds an operand chunk already transposed.
+// A[m][i] B[brow(m)][j], m < *M_dev (or M_max), A row stride lda, B row stride ldb, i < I, j < J
+// (multiples of 4; rows 16-byte aligned).  Chunks past the last row write nothing
+// (launch_sum_parts reads only the chunks in use).  The contraction runs over rows: a thread
+// reads 8 rows of one column back from LDS and holds an operand fragment already transposed.
 // ------------------------------------------------------------------------------------------
-template <int ROWS, int SLOTS>
-struct ColLoader {
-  const float* X;
-  const int32_t* rows;  // row table, or null
-  int ld, col0, ncol, m_begin, m_end;
-  __device__ __forceinline__ static int row(int s) { return (threadIdx.x + 256 * s) % ROWS; }
-  __device__ __forceinline__ static int chunk(int s) { return (threadIdx.x + 256 * s) / ROWS; }
-  __device__ __forceinline__ void load(int step, int s, float (&v)[8]) const {
-    // every load is issued, from a row and column inside the operand; values outside become
-    // zero afterwards (a condition around each load makes the compiler wait for them in turn:
-    // 13,000 cycles per step against about 1,500)
-    const int c = col0 + row(s), m = m_begin + 32 * step + 8 * chunk(s);
-    const float* p = X + min(c, ncol - 1);
-    int r[8];
-    static_for<8>([&](auto e) { r[e] = min(m + e, m_end - 1); });
-    if (rows) static_for<8>([&](auto e) { r[e] = rows[r[e]]; });  // uniform per launch
-    static_for<8>([&](auto e) { v[e] = p[(size_t)r[e] * ld]; });
-    static_for<8>([&](auto e) { v[e] = c < ncol && m + e < m_end ? v[e] : 0.f; });
+// One operand: a step is 32 rows x COLS floats in LDS, the 16-byte chunk c of row r at
+// c ^ 4 (r / 8 % 4), so the four row groups of a fragment read fall on distinct banks.
+template <int COLS, bool TABLE>
+struct ColDma {
+  static constexpr int RPL = 256 / COLS;      // rows per 1 KB load
+  static constexpr int LOADS = 32 / RPL / 4;  // per wavefront (4 wavefronts)
+  const float* X;                             // column col0
+  const int32_t* rows;                        // TABLE: the chunk's rows, in LDS
+  int ld, ncol, m_begin, count;               // columns from col0 on; rows
+  // row r of a step and its columns from col on: this lane's part of load i
+  __device__ __forceinline__ static int first(int i) { return (4 * i + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * RPL; }
+  __device__ __forceinline__ static int row(int i) { return first(i) + (threadIdx.x & 63) / (COLS / 4); }
+  __device__ __forceinline__ int col(int i) const {  // past the last: repeated, its results are not stored
+    return min(4 * (((threadIdx.x & 63) % (COLS / 4)) ^ (4 * (row(i) >> 3))), ncol - 4);
+  }
+  __device__ __forceinline__ void dma(int step, float* dst) const {
+    static_for<LOADS>([&](auto i) {
+      bf16_t* to = reinterpret_cast<bf16_t*>(dst + first(i) * COLS);
+      if constexpr (TABLE) {
+        const int m = min(32 * step + row(i), count - 1);
+        const int r = __builtin_bit_cast(int, *reinterpret_cast<const bf16x2_t*>(rows + m));
+        dma16(X + (size_t)r * ld + col(i), to);
+      } else if (32 * step + 32 <= count) {  // a uniform base and a lane's offset, the same in every step
+        dma16(X + (size_t)(m_begin + 32 * step) * ld + ((uint32_t)row(i) * ld + col(i)), to);
+      } else {  // rows past the last repeat it: get() clears them
+        dma16(X + (size_t)(m_begin + min(32 * step + row(i), count - 1)) * ld + col(i), to);
+      }
+    });
+  }
+  // rows 8 kg .. 8 kg + 7 of column c; unless the step is full, those past its first `left` as zeros
+  template <class Full>
+  __device__ __forceinline__ static void get(Full full, const float* src, int kg, int c, int left, float (&v)[8]) {
+    static_for<8>([&](auto e) {
+      const float x = __builtin_bit_cast(
+          float, *reinterpret_cast<const bf16x2_t*>(src + (8 * kg + e) * COLS + (c ^ (16 * kg))));
+      v[e] = full || 8 * kg + e < left ? x : 0.f;
+    });
   }
 };
 
 template <class TL>
-__global__ void __launch_bounds__(TL::THREADS, 2) tn_ops_kernel(const float* __restrict__ A, const int32_t* __restrict__ arow,
-                                                             int lda, const float* __restrict__ B,
+constexpr int TN_STAGE = (TL::BM + TL::BN) * 32;  // floats of a step
+
+// acc += the tile's products over the chunk's rows.  Operands go to LDS as they are, by direct
+// global->LDS loads two steps ahead, and each wavefront splits its own fragments.  What bounds
+// it is the latency of a step's loads (the chunk is a serial chain and the shapes give one or
+// two blocks per CU), so the loads in flight count and not the split being done twice.  A
+// training step of 4 clips of 5 x 240 x 432 (256 wide, 8 blocks; bf16) and of 2 (FP32), all
+// weight gradients: loads into registers one step ahead, split once into LDS, 64 x 64 tiles
+// 5.2 and 5.5 ms; direct loads, split once through LDS 3.7 and 4.3 ms; this 3.5 and 3.3 ms.
+template <class TL, class LA, class LW>
+__device__ __forceinline__ void tn_core(const LA& la, const LW& lw, float* lds, f32x4_t (&acc)[TL::FM][TL::FN]) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int wm = wv >> 1, wn = wv & 1, l16 = lane & 15, kg = lane >> 4;
+  const int steps = (la.count + 31) / 32;
+  static_for<TL::FM>([&](auto i) {
+    static_for<TL::FN>([&](auto j) { acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; });
+  });
+  auto issue = [&](int step) {
+    float* dst = lds + (step & 1) * TN_STAGE<TL>;
+    la.dma(step, dst);
+    lw.dma(step, dst + TL::BM * 32);
+  };
+  auto multiply = [&](int step, auto full) {
+    const float* src = lds + (step & 1) * TN_STAGE<TL>;
+    const int left = la.count - 32 * step;
+    bf16x8_t af[TL::NP][TL::FM], wf[TL::FN][TL::NP];
+    static_for<TL::FM>([&](auto i) {
+      float v[8];
+      la.get(full, src, kg, wm * 16 * TL::FM + 16 * i + l16, left, v);
+      ops_split<TL::NP>(v, [&](auto p, bf16x8_t x) { af[p][i] = x; });
+    });
+    static_for<TL::FN>([&](auto j) {
+      float v[8];
+      lw.get(full, src + TL::BM * 32, kg, wn * 16 * TL::FN + 16 * j + l16, left, v);
+      ops_split<TL::NP>(v, [&](auto p, bf16x8_t x) { wf[j][p] = x; });
+    });
+    lds_barrier();  // every wavefront has read the step
+    if (step + 2 < steps) issue(step + 2);
+    static_for<TL::FN>([&](auto j) { ops_products<TL>(af, wf[j], acc, j); });
+  };
+  issue(0);
+  if (steps > 1) issue(1);
+  for (int step = 0; step + 1 < steps; ++step) {
+    vm_wait_barrier<LA::LOADS + LW::LOADS>();  // this step has landed, the next is on its way
+    multiply(step, std::true_type{});
+  }
+  vm_wait_barrier<0>();
+  multiply(steps - 1, std::false_type{});
+}
+
+template <class TL, bool TABLE>
+__global__ void __launch_bounds__(TL::THREADS, 2) tn_ops_kernel(const float* __restrict__ A, int lda, const float* __restrict__ B,
                                                              const int32_t* __restrict__ brow, int ldb,
                                                              const int32_t* __restrict__ M_dev, int M_max, int I, int J,
-                                                             float* __restrict__ part) {
-  __shared__ __align__(16) bf16_t lds[TL::NP * TL::PLANE];
+                                                             int chunk, float* __restrict__ part) {
+  extern __shared__ __align__(16) float tn_lds[];
   const int M = M_dev ? M_dev[0] : M_max;
-  // the tiles of a chunk run on one XCD (xcd_tile), so its rows enter that XCD's L2 once
-  const int it = (I + TL::BM - 1) / TL::BM;
-  int ch, tile;
-  xcd_tile(blockIdx.x, it * ((J + TL::BN - 1) / TL::BN), ch, tile);
-  const int m_begin = ch * TN_CHUNK, m_end = min(M, m_begin + TN_CHUNK);
-  if (m_begin >= m_end) return;  // uniform per block
+  // Each XCD (block b runs on b & 7) takes an eighth of the tiles that have rows, in the order
+  // of the chunks: those of a chunk share its L2, and no XCD has a whole chunk more to do than
+  // another (FP32, 64 x 64 tiles: 105 -> 99 us per call of the step below).
+  const int it = (I + TL::BM - 1) / TL::BM, tiles = it * ((J + TL::BN - 1) / TL::BN);
+  const int total = (M + chunk - 1) / chunk * tiles, per = (total + 7) / 8;
+  const int k = blockIdx.x >> 3, idx = (blockIdx.x & 7) * per + k;
+  if (k >= per || idx >= total) return;  // uniform per block
+  const int ch = idx / tiles, tile = idx % tiles;
+  const int m_begin = ch * chunk, m_end = min(M, m_begin + chunk);
   const int i0 = (tile % it) * TL::BM, j0 = (tile / it) * TL::BN;
-  const ColLoader<TL::BM, TL::SA> la{A, arow, lda, i0, I, m_begin, m_end};
-  const ColLoader<TL::BN, TL::SW> lw{B, brow, ldb, j0, J, m_begin, m_end};
+  // a row table (B's) is brought to LDS first: a load that has to wait for its row number would
+  // also wait for every load queued before it
+  int32_t* table = reinterpret_cast<int32_t*>(tn_lds + 2 * TN_STAGE<TL>);
+  if constexpr (TABLE) {
+    for (int m = threadIdx.x; m < m_end - m_begin; m += TL::THREADS) table[m] = brow[m_begin + m];
+    __syncthreads();
+  }
+  const ColDma<TL::BM, false> la{A + i0, nullptr, lda, I - i0, m_begin, m_end - m_begin};
+  const ColDma<TL::BN, TABLE> lw{B + j0, table, ldb, J - j0, m_begin, m_end - m_begin};
   f32x4_t acc[TL::FM][TL::FN];
-  ops_core<TL>(la, lw, (m_end - m_begin + 31) / 32, lds, acc);
+  tn_core<TL>(la, lw, tn_lds, acc);
   ops_mend<TL>(acc, [&](int ir, int jr) {
     const int i = i0 + ir, j = j0 + jr;
     if (i >= I || j >= J) return 0.f;
     float y = 0.f;
     for (int m = m_begin; m < m_end; ++m)
-      y = fmaf(A[(size_t)(arow ? arow[m] : m) * lda + i], B[(size_t)(brow ? brow[m] : m) * ldb + j], y);
+      y = fmaf(A[(size_t)m * lda + i], B[(size_t)(TABLE ? brow[m] : m) * ldb + j], y);
     return y;
   });
   // lane holds P[i = .. + l16][j = .. + 4 kg + e]
@@ -321,26 +418,37 @@ __global__ void __launch_bounds__(TL::THREADS, 2) tn_ops_kernel(const float* __r
   });
 }
 
-// 64 x 64 tiles: a block's chunk is a serial chain of up to 64 steps, each waiting for rows
-// from HBM, so many small blocks beat the halved operand traffic of 128 x 128 tiles (4 clips
-// of 5 x 240 x 432, 256-wide, bf16 operands: 104 us a launch against 172 us).
+// 128 x 128 tiles halve the operand bytes where that leaves a block for every CU (a row count
+// known only on the device is taken as 0.4 of its bound; the bf16 step above with 64 x 64 tiles
+// alone: 4.7 ms, with both 3.7), else 64 x 64.  A row table takes the small tile: only the query
+// weights' C x C gradients have one.
 template <int NP>
-static void tn_ops(const float* A, const int32_t* arow, int lda, const float* B, const int32_t* brow, int ldb,
-                   const int32_t* M_dev, int M_max, int I, int J, float* part, hipStream_t s) {
-  using TL = OpsTile<64, 64, NP>;
+static void tn_ops(const float* A, int lda, const float* B, const int32_t* brow, int ldb, const int32_t* M_dev,
+                   int M_max, int I, int J, int chunk, float* part, hipStream_t s) {
   if (M_max <= 0) return;
-  const int grid = xcd_grid(tn_chunks(M_max), ((I + TL::BM - 1) / TL::BM) * ((J + TL::BN - 1) / TL::BN));
-  tn_ops_kernel<TL><<<grid, TL::THREADS, 0, s>>>(A, arow, lda, B, brow, ldb, M_dev, M_max, I, J, part);
+  const int chunks = (M_max + chunk - 1) / chunk;
+  auto run = [&](auto tl, auto has_table) {
+    using TL = decltype(tl);
+    constexpr bool TABLE = decltype(has_table)::value;
+    const size_t bytes = 2 * TN_STAGE<TL> * 4 + (TABLE ? (size_t)chunk * 4 : 0);
+    ops_allow_lds(tn_ops_kernel<TL, TABLE>, bytes);
+    const int tiles = ((I + TL::BM - 1) / TL::BM) * ((J + TL::BN - 1) / TL::BN);
+    const int grid = 8 * ((chunks * tiles + 7) / 8);
+    tn_ops_kernel<TL, TABLE><<<grid, TL::THREADS, bytes, s>>>(A, lda, B, brow, ldb, M_dev, M_max, I, J, chunk, part);
+  };
+  const long long blocks = (long long)((I + 127) / 128) * ((J + 127) / 128) * chunks;
+  const bool big = J > 64 && (M_dev ? 2 * blocks / 5 : blocks) >= 256;
+  if (brow)
+    run(OpsTile<64, 64, NP>(), std::true_type());
+  else if (big)
+    run(OpsTile<128, 128, NP>(), std::false_type());
+  else
+    run(OpsTile<64, 64, NP>(), std::false_type());
 }
 
-void launch_tn_f32(const float* A, const int32_t* arow, int lda, const float* B, const int32_t* brow, int ldb,
-                   const int32_t* M_dev, int M_max, int I, int J, float* part, hipStream_t s) {
-  tn_ops<3>(A, arow, lda, B, brow, ldb, M_dev, M_max, I, J, part, s);
-}
-
-void launch_tn_bf16ops(const float* A, const int32_t* arow, int lda, const float* B, const int32_t* brow, int ldb,
-                       const int32_t* M_dev, int M_max, int I, int J, float* part, hipStream_t s) {
-  tn_ops<1>(A, arow, lda, B, brow, ldb, M_dev, M_max, I, J, part, s);
+void launch_tn(bool bf16, const float* A, int lda, const float* B, const int32_t* brow, int ldb, const int32_t* M_dev,
+               int M_max, int I, int J, float* part, hipStream_t s) {
+  (bf16 ? tn_ops<1> : tn_ops<3>)(A, lda, B, brow, ldb, M_dev, M_max, I, J, tn_chunk(bf16), part, s);
 }
 
 }  // namespace dr

@@ -43,3 +43,30 @@ def test_infinite_output_gradient_gives_infinite_weight_gradient():
     hit[:, 1, 1, 2] = True
     assert np.isinf(g.numpy()[hit]).all()
     assert np.isfinite(g.numpy()[~hit]).all()
+
+
+@pytest.mark.parametrize("precision,clips", [("fp32", 5), ("bf16", 9)])
+def test_weight_gradients_of_a_batch_are_the_sum_over_its_clips(precision, clips):
+    """The batch's weight gradients take the 128 x 128 tiles (a last chunk and a last step with
+    few rows), one clip's the 64 x 64 tiles; only the order of the FP32 sums differs: chunks of
+    up to 2048 terms, so 2e-5 of a tensor's largest entry leaves a factor of ten."""
+    from paper_2509_10466_amd import Inpainter
+    from paper_2509_10466_amd.api import unflatten_params
+    eng = Inpainter(MID, drsynth.make_weights(MID, 1))
+    eng.train_precision(precision)
+    f, m = _clips(clips, 240, 432)
+    gen = torch.Generator(device="cuda").manual_seed(0)
+    dpred = torch.randn(f.shape, generator=gen, device="cuda")
+
+    def grads(part):
+        pred, saved = eng.train_forward(f[part].contiguous(), m[part].contiguous())
+        g = eng.train_backward(saved, dpred[part].contiguous()).double().cpu()
+        saved.close()
+        return g
+
+    whole = unflatten_params(MID, grads(slice(None)))
+    summed = unflatten_params(MID, sum(grads(slice(b, b + 1)) for b in range(clips)))
+    top = max(float(v.abs().max()) for v in summed.values())
+    for name, want in summed.items():
+        err = float((whole[name] - want).abs().max())
+        assert err <= 2e-5 * float(want.abs().max()) + 1e-7 * top, (name, err)
