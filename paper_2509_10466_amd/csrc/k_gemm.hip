@@ -17,6 +17,8 @@
 //                                                projection (compact rows)
 //   proj:  x[idx[r]] += o W_o^T + b_o;  u2[r] = normalise(x[idx[r]])
 //   fc2:   x[idx[r]] += h W_2^T + b_2;  x^[idx[r]] = normalise(x[idx[r]])
+#include <algorithm>
+
 #include "dr_internal.h"
 #include "gemm_core.h"
 
@@ -534,7 +536,7 @@ void launch_resid_ln_bf16(int m_max, const int32_t* m_dev, int C, int K, const b
 }
 
 // ------------------------------------------------------------------------------------------
-// Fused post-attention block over 64 query rows (compact rows r, token idx[r]):
+// Fused post-attention block over 64 (or 32) query rows (compact rows r, token idx[r]):
 //   x1 = x + o W_o^T + b_o        u2 = normalise(x1)
 //   h  = GELU(u2 W1'^T + b1')     (hidden chunks of HC columns)
 //   x2 = x1 + h W_2^T + b_2       x^ = normalise(x2)
@@ -548,9 +550,16 @@ void launch_resid_ln_bf16(int m_max, const int32_t* m_dev, int C, int K, const b
 // while the other waits on LDS or the barrier.
 // ------------------------------------------------------------------------------------------
 constexpr int MLP_THREADS = 512;
+// A block's chain of weight stages takes 28 us at dim 256 with 64 rows, however few blocks there
+// are, and 21 us with 32 (half the products, fragment reads of rows and GELU per stage, the same
+// weight stream).  So rows are split over 32-row blocks while every one of them has a CU of its
+// own (one 5 x 240 x 432 stream, ~1,700 query rows: 465 -> 412 us per frame); beyond 256 of them
+// a second turn (42 us) would cost more than 64-row blocks do (30 us).
+constexpr int MLP_SMALL_BLOCKS = 256;
 
 template <int C_, int HC_, int BM_ = 64, int ST_ = 3, int SR_ = 0>
 struct MlpCfg {
+  using Small = MlpCfg<C_, HC_, 32, ST_, SR_>;
   static constexpr int C = C_, HC = HC_, BM = BM_, R = 4 * C, ST = ST_;
   static constexpr int WM = 2, WN = 4, TM = BM / WM;   // wavefront grid; rows per wavefront
   static constexpr int FM = TM / 16;
@@ -587,7 +596,7 @@ struct MlpCfg {
   static_assert((BM == 32 || BM == 64) && (ST == 2 || ST == 3), "row tile and ring depth");
   // x1 (the residual after the projection) kept in registers for the second residual, rather
   // than stored to x and read back, where the registers allow it
-  static constexpr bool X1_REGS = C <= 256;
+  static constexpr bool X1_REGS = C <= 256 || BM == 32;
   static_assert(LDS_BYTES <= 160 * 1024, "LDS");
 };
 
@@ -681,13 +690,11 @@ __device__ __forceinline__ void resid_rows(f32x4_t (&acc)[MC::FM][MC::FN_C], con
 }
 
 template <class MC>
-__global__ void __launch_bounds__(MLP_THREADS) mlp_block_kernel(const int32_t* __restrict__ m_dev,
-                                                                const bf16* __restrict__ o,
-                                                                const int32_t* __restrict__ rows,
-                                                                const bf16* __restrict__ Wo, const float* __restrict__ bo,
-                                                                const bf16* __restrict__ W1, const float* __restrict__ b1,
-                                                                const bf16* __restrict__ W2, const float* __restrict__ b2,
-                                                                float* __restrict__ x, bf16* __restrict__ xh) {
+__device__ __forceinline__ void mlp_block(int M, const bf16* __restrict__ o, const int32_t* __restrict__ rows,
+                                          const bf16* __restrict__ Wo, const float* __restrict__ bo,
+                                          const bf16* __restrict__ W1, const float* __restrict__ b1,
+                                          const bf16* __restrict__ W2, const float* __restrict__ b2,
+                                          float* __restrict__ x, bf16* __restrict__ xh) {
   constexpr int C = MC::C, HC = MC::HC, R = MC::R, BM = MC::BM, NW = MLP_THREADS / 64;
   extern __shared__ __align__(16) bf16 lds[];
   bf16* ring = lds;
@@ -699,7 +706,6 @@ __global__ void __launch_bounds__(MLP_THREADS) mlp_block_kernel(const int32_t* _
   float(*red)[MC::WN][MC::BM] = reinterpret_cast<float(*)[MC::WN][MC::BM]>(sb2 + C);
   int* sdst = reinterpret_cast<int*>(sb2 + C + 2 * MC::WN * BM);
 
-  const int M = m_dev[0];
   const int m0 = blockIdx.x * BM;
   if (m0 >= M) return;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
@@ -976,17 +982,35 @@ __global__ void __launch_bounds__(MLP_THREADS) mlp_block_kernel(const int32_t* _
   });
 }
 
+// The row count is known on the device only, so the kernel holds both row tiles (MLP_SMALL_BLOCKS;
+// next to a kernel with the larger one alone that costs the larger one at most 0.4 % of a clip).
+template <class MC>
+__global__ void __launch_bounds__(MLP_THREADS) mlp_block_kernel(const int32_t* __restrict__ m_dev,
+                                                                const bf16* __restrict__ o,
+                                                                const int32_t* __restrict__ rows,
+                                                                const bf16* __restrict__ Wo, const float* __restrict__ bo,
+                                                                const bf16* __restrict__ W1, const float* __restrict__ b1,
+                                                                const bf16* __restrict__ W2, const float* __restrict__ b2,
+                                                                float* __restrict__ x, bf16* __restrict__ xh) {
+  const int M = m_dev[0];
+  if (M <= 32 * MLP_SMALL_BLOCKS)
+    mlp_block<typename MC::Small>(M, o, rows, Wo, bo, W1, b1, W2, b2, x, xh);
+  else
+    mlp_block<MC>(M, o, rows, Wo, bo, W1, b1, W2, b2, x, xh);
+}
+
 template <class MC>
 static void mlp_launch(int m_max, const int32_t* m_dev, const bf16* o, const int32_t* rows, const bf16* wo,
                        const float* bo, const bf16* w1, const float* b1, const bf16* w2, const float* b2, float* x,
                        bf16* xh, hipStream_t s) {
+  constexpr size_t bytes = std::max(MC::LDS_BYTES, MC::Small::LDS_BYTES);
   static bool attr = false;
   if (!attr) {
-    allow_lds(mlp_block_kernel<MC>, MC::LDS_BYTES);
+    allow_lds(mlp_block_kernel<MC>, bytes);
     attr = true;
   }
-  mlp_block_kernel<MC><<<(m_max + MC::BM - 1) / MC::BM, MLP_THREADS, MC::LDS_BYTES, s>>>(m_dev, o, rows, wo, bo, w1,
-                                                                                          b1, w2, b2, x, xh);
+  const int grid = std::max((m_max + MC::BM - 1) / MC::BM, std::min((m_max + 31) / 32, MLP_SMALL_BLOCKS));
+  mlp_block_kernel<MC><<<grid, MLP_THREADS, bytes, s>>>(m_dev, o, rows, wo, bo, w1, b1, w2, b2, x, xh);
 }
 
 bool mlp_block_supported(int C, int R) { return R == 4 * C && (C == 64 || C == 128 || C == 256 || C == 384); }

@@ -41,3 +41,19 @@ def test_fp8_row_lengths(dim, ratio):
     out = Inpainter(cfg, W)(torch.from_numpy(f).cuda(), torch.from_numpy(m).cuda(), "fp8").cpu().numpy()
     compare(out, on.forward(f, m, W, cfg), f, m, TOL["fp8"])
     assert np.isfinite(out).all()
+
+
+@pytest.mark.parametrize("net", ["tiny64", "mid", "clip240", "clip720"])
+def test_mlp_rows_per_block_agree_bitwise(net):
+    """Ten clips have more than 8,192 query rows (64-row MLP tiles), one has not (32-row tiles),
+    with ragged last tiles on both sides."""
+    from paper_2509_10466_amd import Inpainter
+    cfg = MID if net == "mid" else dataclasses.replace(drsynth.NETS[net], blocks=2)
+    H, W, n = (4 * cfg.win_h * 6, 4 * cfg.win_w * 6, 10 if cfg.win_t > 1 else 80)
+    eng = Inpainter(cfg, drsynth.make_weights(cfg, 1))
+    f, m = drsynth.make_clip_batch(range(n), cfg.win_t, H, W)
+    assert m.reshape(n, cfg.win_t, H // 4, 4, W // 4, 4).any((3, 5)).sum() > 8192
+    f, m = torch.from_numpy(f).cuda(), torch.from_numpy(m).cuda()
+    whole = eng(f, m, "bf16")
+    for b in (0, n - 1):
+        assert torch.equal(eng(f[b:b + 1].contiguous(), m[b:b + 1].contiguous(), "bf16")[0], whole[b])
