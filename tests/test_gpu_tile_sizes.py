@@ -45,7 +45,7 @@ def test_fp8_row_lengths(dim, ratio):
 
 @pytest.mark.parametrize("net", ["tiny64", "mid", "clip240", "clip720"])
 def test_mlp_rows_per_block_agree_bitwise(net):
-    """Ten clips have more than 8,192 query rows (64-row MLP tiles), one has not (32-row tiles),
+    """Ten clips (80 of one frame) have more than 8,192 query rows (64-row MLP tiles), one has not (32-row tiles),
     with ragged last tiles on both sides."""
     from paper_2509_10466_amd import Inpainter
     cfg = MID if net == "mid" else dataclasses.replace(drsynth.NETS[net], blocks=2)
