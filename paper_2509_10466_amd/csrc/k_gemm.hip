@@ -828,9 +828,9 @@ __device__ __forceinline__ void mlp_block(int M, const bf16* __restrict__ o, con
       static_for<MC::FM>([&](auto i) { fa[q][i] = lds_frag(tile, wm * MC::TM + 16 * i, q); });
     }
   };
-  // The products of slice q of stage s; `between` runs after the first of them (its operands are
-  // read again by later ones, so no register that `between` writes is still an operand of a
-  // product in flight).
+  // The products of slice q of stage s; `between` runs after the first of them, whose operands
+  // stay allocated to the end, so that nothing `between` writes shares a register that the
+  // product in flight still reads.
   auto multiply = [&](auto s, auto q, auto&& between) {
     mfma_fence_begin();
     bool first = true;
@@ -853,6 +853,8 @@ __device__ __forceinline__ void mlp_block(int M, const bf16* __restrict__ o, con
           });
         });
       });
+      mfma_fence_end();
+      asm volatile("" ::"v"(fw[q][0]), "v"(ua[tt * MC::KB1 + q * MC::KB1 / 2][q * MC::KB1 % 2][0]));
     } else {
       constexpr int j0 = (s < S1 ? s % MC::NHALF : MC::half2(s)) * MC::FPH;
       static_for<MC::FM>([&](auto i) {
@@ -861,8 +863,9 @@ __device__ __forceinline__ void mlp_block(int M, const bf16* __restrict__ o, con
           after_first();
         });
       });
+      mfma_fence_end();
+      asm volatile("" ::"v"(fw[q][0]), "v"(fa[q][0]));
     }
-    mfma_fence_end();
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;

@@ -542,6 +542,10 @@ __global__ void __launch_bounds__(256) embed_ovl_bf16_kernel(Geo g, const float*
 #pragma unroll
       for (int e = 0; e < 8; ++e) pk[3 * r + part][e] = (__bf16)v[8 * part + e];
   }
+  // the conversions are done here, not sunk between the products below, where they would write
+  // operands of a product in flight
+#pragma unroll
+  for (int sl = 0; sl < KS; ++sl) asm volatile("" : "+v"(pk[sl]));
   f32x4_t acc[FN];
   float sum = 0.f;
 #pragma unroll
