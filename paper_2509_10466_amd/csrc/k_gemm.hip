@@ -613,18 +613,18 @@ __device__ __forceinline__ int res_off(int r, int c) {
   return (c >> 6) * (BM * 64) + r * 64 + ((((c & 63) >> 3) ^ lds_swz(r)) << 3) + (c & 7);
 }
 
-// This thread's residual values x[dst] for the [64][C] accumulators (zero for rows past M),
-// loaded ahead of the epilogue so that their latency overlaps the last k stage.
+// This thread's residual values x[row] for the [BM][C] accumulators: FM * FN_C loads of every
+// wavefront, whatever its rows (the counted waits rely on that; of native vectors, since the
+// compiler's vectoriser moves the four loads of a float4 struct to where they are used).
 template <class MC>
-__device__ __forceinline__ void load_resid(const float* __restrict__ x, const int (&dst)[MC::FM],
-                                           float4 (&xo)[MC::FM][MC::FN_C]) {
+__device__ __forceinline__ void load_resid(const float* __restrict__ x, const int (&row)[MC::FM],
+                                           f32x4_t (&xo)[MC::FM][MC::FN_C]) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int wn = wv % MC::WN, kg = lane >> 4;
   static_for<MC::FM>([&](auto i) {
     static_for<MC::FN_C>([&](auto j) {
       const int n = MC::col(wn, j) + 4 * kg;
-      xo[i][j] = dst[i] >= 0 ? *reinterpret_cast<const float4*>(x + (size_t)dst[i] * MC::C + n)
-                             : make_float4(0.f, 0.f, 0.f, 0.f);
+      xo[i][j] = *reinterpret_cast<const f32x4_t*>(x + (size_t)row[i] * MC::C + n);
     });
   });
 }
@@ -635,7 +635,7 @@ __device__ __forceinline__ void load_resid(const float* __restrict__ x, const in
 template <class MC>
 __device__ __forceinline__ void resid_rows(f32x4_t (&acc)[MC::FM][MC::FN_C], const float* sbias,
                                            float* __restrict__ x, const int (&dst)[MC::FM],
-                                           const float4 (&xo_in)[MC::FM][MC::FN_C], float (*red)[MC::WN][MC::BM],
+                                           const f32x4_t (&xo_in)[MC::FM][MC::FN_C], float (*red)[MC::WN][MC::BM],
                                            float (&mean)[MC::FM], float (&rstd)[MC::FM], bool store = true) {
   constexpr int C = MC::C, FN = MC::FN_C;
   // the thread index passes through an empty asm so that the column addresses below are
@@ -650,12 +650,12 @@ __device__ __forceinline__ void resid_rows(f32x4_t (&acc)[MC::FM][MC::FN_C], con
     float sum = 0.f;
     static_for<FN>([&](auto j) {
       const int n = MC::col(wn, j) + 4 * kg;
-      const float4 xo = xo_in[i][j];
+      const f32x4_t xo = xo_in[i][j];
       f32x4_t& a = acc[i][j];
-      a[0] += sbias[n] + xo.x;
-      a[1] += sbias[n + 1] + xo.y;
-      a[2] += sbias[n + 2] + xo.z;
-      a[3] += sbias[n + 3] + xo.w;
+      a[0] += sbias[n] + xo[0];
+      a[1] += sbias[n + 1] + xo[1];
+      a[2] += sbias[n + 2] + xo[2];
+      a[3] += sbias[n + 3] + xo[3];
       if (store && dst[i] >= 0)
         *reinterpret_cast<float4*>(x + (size_t)dst[i] * C + n) = make_float4(a[0], a[1], a[2], a[3]);
       sum += (a[0] + a[1]) + (a[2] + a[3]);
@@ -713,27 +713,22 @@ __device__ __forceinline__ void mlp_block(int M, const bf16* __restrict__ o, con
   const int l16 = lane & 15, kg = lane >> 4;
 
   // the rows' token indices first: the residual loads below need them
-  int dst[MC::FM];
-  static_for<MC::FM>([&](auto i) {
-    const int m = m0 + wm * MC::TM + 16 * i + l16;
-    dst[i] = m < M ? rows[m] : -1;
-  });
+  int row[MC::FM];
+  static_for<MC::FM>([&](auto i) { row[i] = rows[min(m0 + wm * MC::TM + 16 * i + l16, M - 1)]; });
   // the biases into registers now, into LDS after the loads below are queued: one round trip
   // for all of them instead of one per loop iteration
   constexpr int NBC = (C + MLP_THREADS - 1) / MLP_THREADS, NBR = (R + MLP_THREADS - 1) / MLP_THREADS;
   float vbo[NBC], vb2[NBC], vb1[NBR];
   static_for<NBC>([&](auto k) {
-    const int i = t + MLP_THREADS * k;
-    vbo[k] = i < C ? bo[i] : 0.f;
-    vb2[k] = i < C ? b2[i] : 0.f;
+    const int i = min(t + MLP_THREADS * k, C - 1);
+    vbo[k] = bo[i];
+    vb2[k] = b2[i];
   });
-  static_for<NBR>([&](auto k) {
-    const int i = t + MLP_THREADS * k;
-    vb1[k] = i < R ? b1[i] : 0.f;
-  });
+  static_for<NBR>([&](auto k) { vb1[k] = b1[min(t + MLP_THREADS * k, R - 1)]; });
+  const int uwv = __builtin_amdgcn_readfirstlane(wv);
   // o rows -> resident A tile (rows >= M read row M-1; their results are never stored):
   // 8 rows per load, BM / 8 row groups per k block, one group per wavefront
-  if (wv * 8 < BM)
+  if (BM == 8 * NW || uwv * 8 < BM)
     static_for<MC::NKC>([&](auto kb) {
       const int row = wv * 8 + (lane >> 3);
       const int m = min(m0 + row, M - 1);
@@ -750,7 +745,6 @@ __device__ __forceinline__ void mlp_block(int M, const bf16* __restrict__ o, con
   // uniform address, so a load needs no vector arithmetic and two registers serve every stage
   const int lrow = wv * 8 + (lane >> 3), lcol = ((lane & 7) ^ lds_swz(lrow)) * 16;
   const uint32_t off_c = lrow * C * 2 + lcol, off_r = lrow * R * 2 + lcol;
-  const int uwv = __builtin_amdgcn_readfirstlane(wv);
   auto issue = [&](auto s) {
     const bf16* base;
     constexpr bool w2 = s >= MC::NKC * MC::NHALF && !MC::is_w1(s);
@@ -771,26 +765,34 @@ __device__ __forceinline__ void mlp_block(int M, const bf16* __restrict__ o, con
       dma16(reinterpret_cast<const char*>(base + (size_t)rr * ld + 64 * b) + (w2 ? off_r : off_c), dst + row * 64);
     });
   };
-  static_for<MC::ST - 1>([&](auto s0) { issue(s0); });
-  // the residual rows x[dst] for the projection's epilogue, requested now (after the first
-  // stages) so that their latency hides behind the projection: the first two stage waits
-  // leave these NX loads outstanding, the third covers them
-  float4 xo[MC::FM][MC::FN_C];
-  load_resid<MC>(x, dst, xo);
+  static_for<MC::ST - 1>([&](auto s0) {
+    mfma_fence_begin();  // the loads are counted below in this order
+    issue(s0);
+  });
+  mfma_fence_begin();
+  // the residual rows for the projection's epilogue, requested now (after the first stages) so
+  // that their latency hides behind the projection: the first two stage waits leave these NX
+  // loads outstanding, the third covers them.  Every wavefront issues all of them: were they
+  // guarded by dst, one whose rows are all past M would wait for too little.
+  f32x4_t xo[MC::FM][MC::FN_C];
+  // (the row numbers are first used here: in front of the stages these would wait for them)
+#pragma unroll
+  for (int i = 0; i < MC::FM; ++i) asm volatile("" : "+v"(row[i]));
+  load_resid<MC>(x, row, xo);
   constexpr int NX = MC::FM * MC::FN_C;
+  mfma_fence_begin();
+  int dst[MC::FM];  // -1: a row past M, which repeats row M-1 and stores nothing
+  static_for<MC::FM>([&](auto i) { dst[i] = m0 + wm * MC::TM + 16 * i + l16 < M ? row[i] : -1; });
+  // (threads past the last value repeat it)
   static_for<NBC>([&](auto k) {
-    const int i = t + MLP_THREADS * k;
-    if (i < C) {
-      sbo[i] = vbo[k];
-      sb2[i] = vb2[k];
-    }
+    const int i = min(t + MLP_THREADS * k, C - 1);
+    sbo[i] = vbo[k];
+    sb2[i] = vb2[k];
   });
-  static_for<NBR>([&](auto k) {
-    const int i = t + MLP_THREADS * k;
-    if (i < R) sb1[i] = vb1[k];
-  });
-  // the token rows wait in LDS for the last epilogue (in registers they would be spilled)
-  if (wn == 0 && kg == 0) static_for<MC::FM>([&](auto i) { sdst[wm * MC::TM + 16 * i + l16] = dst[i]; });
+  static_for<NBR>([&](auto k) { sb1[min(t + MLP_THREADS * k, R - 1)] = vb1[k]; });
+  // the token rows wait in LDS for the last epilogue (in registers they would be spilled); the
+  // wavefronts and lane groups that share a row write the same value
+  static_for<MC::FM>([&](auto i) { sdst[wm * MC::TM + 16 * i + l16] = dst[i]; });
   f32x4_t acc[MC::FM][MC::FN_C], hacc[MC::FM][MC::FN_H];
   static_for<MC::FM>([&](auto i) {
     static_for<MC::FN_C>([&](auto j) { acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; });
@@ -917,7 +919,7 @@ __device__ __forceinline__ void mlp_block(int M, const bf16* __restrict__ o, con
   resid_rows<MC>(acc, sbo, x, dst, xo, red, mean, rstd, !MC::X1_REGS);
   if constexpr (MC::X1_REGS)
     static_for<MC::FM>([&](auto i) {
-      static_for<MC::FN_C>([&](auto j) { xo[i][j] = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]); });
+      static_for<MC::FN_C>([&](auto j) { xo[i][j] = acc[i][j]; });
     });
   static_for<MC::FM>([&](auto i) {
     const int r = wm * MC::TM + 16 * i + l16;
@@ -969,8 +971,11 @@ __device__ __forceinline__ void mlp_block(int M, const bf16* __restrict__ o, con
     static_for<MC::NKH * MC::NHALF>([&](auto u) { stage(std::integral_constant<int, s2 + u>{}, I0{}, true, true); });
   });
   // x2 = x1 + h W_2^T + b_2; x^ = normalise(x2)
-  static_for<MC::FM>([&](auto i) { dst[i] = sdst[wm * MC::TM + 16 * i + l16]; });
-  if constexpr (!MC::X1_REGS) load_resid<MC>(x, dst, xo);  // this thread's own stores, an L2 hit
+  static_for<MC::FM>([&](auto i) {
+    dst[i] = sdst[wm * MC::TM + 16 * i + l16];
+    row[i] = max(dst[i], 0);
+  });
+  if constexpr (!MC::X1_REGS) load_resid<MC>(x, row, xo);  // this thread's own stores, an L2 hit
   resid_rows<MC>(acc, sb2, x, dst, xo, red, mean, rstd);
   static_for<MC::FM>([&](auto i) {
     if (dst[i] >= 0)

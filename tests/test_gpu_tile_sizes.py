@@ -57,3 +57,25 @@ def test_mlp_rows_per_block_agree_bitwise(net):
     whole = eng(f, m, "bf16")
     for b in (0, n - 1):
         assert torch.equal(eng(f[b:b + 1].contiguous(), m[b:b + 1].contiguous(), "bf16")[0], whole[b])
+
+
+@pytest.mark.parametrize("net", ["tiny64", "mid", "clip240", "clip720"])
+@pytest.mark.parametrize("rest", [1, 15, 16, 17, 31])
+def test_mlp_last_block_of_any_length(net, rest):
+    """A last block of 1 to 31 query rows (wavefronts without a row below 17) against the same
+    rows in front of another clip's, in 32-row blocks and, behind 8,192 others, in 64-row ones."""
+    from paper_2509_10466_amd import Inpainter
+    cfg = MID if net == "mid" else dataclasses.replace(drsynth.NETS[net], blocks=2)
+    n = 10 if cfg.win_t > 1 else 80
+    H, W = 4 * cfg.win_h * 6, 4 * cfg.win_w * 6
+    eng = Inpainter(cfg, drsynth.make_weights(cfg, 1))
+    f, m = drsynth.make_clip_batch(range(n), cfg.win_t, H, W)
+    m[0] = 0
+    tokens = np.random.default_rng(rest).choice(cfg.win_t * (H // 4) * (W // 4), 64 + rest, replace=False)
+    t, i, j = np.unravel_index(tokens, (cfg.win_t, H // 4, W // 4))
+    m[0, t, 4 * i + 1, 4 * j + 2] = 1
+    f, m = torch.from_numpy(f).cuda(), torch.from_numpy(m).cuda()
+    alone = eng(f[:1].contiguous(), m[:1].contiguous(), "bf16")
+    assert not torch.equal(alone, f[:1])
+    for k in (2, n):
+        assert torch.equal(eng(f[:k].contiguous(), m[:k].contiguous(), "bf16")[0], alone[0])

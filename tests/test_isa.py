@@ -74,3 +74,38 @@ def test_operands_of_double_rate_products_are_not_overwritten(listing):
     assert sum(listing.count(op) for op in DOUBLE_RATE) > 1000
     found = overwritten_operands(listing)
     assert not found, "\n".join(" | ".join(f) for f in found[:20])
+
+
+def miscounted_waits(listing, name, stage_loads):
+    """Counted waits (vmcnt(n), n > 0, before a barrier) of the kernels `name` whose n newest
+    vector-memory operations are not all issued on every path, or hold more direct loads to LDS
+    than the one stage that may be on its way: (kernel, n, direct loads or None for a branch)."""
+    found, kernel, ops = [], None, []
+    lines = [line.split("//")[0].strip() for line in listing.splitlines()]
+    for at, line in enumerate(lines):
+        if line.endswith(">:"):
+            kernel, ops = line.split("<")[1][:-2], []
+        elif name not in (kernel or ""):
+            continue
+        elif line.startswith(("s_cbranch", "s_branch")):
+            ops.append("branch")
+        elif line.startswith(("global_", "buffer_", "flat_")):
+            ops.append("dma" if "_lds_" in line else "vmem")
+        elif line.startswith("s_waitcnt") and "vmcnt" in line and lines[at + 1] == "s_barrier":
+            n = int(re.search(r"vmcnt\((\d+)\)", line)[1])
+            newest = ops[len(ops) - n:] if n else []
+            if "branch" in newest or len(newest) < n:
+                found.append((kernel, n, None))
+            elif newest.count("dma") > stage_loads:
+                found.append((kernel, n, newest.count("dma")))
+    return found
+
+
+@pytest.mark.parametrize("dim,stage_loads", [(64, 2), (128, 2), (256, 4), (384, 3)])
+def test_mlp_stage_waits_count_what_every_wavefront_issues(listing, dim, stage_loads):
+    """A stage holds stage_loads direct loads of every wavefront.  The first two waits also leave
+    the residual rows' loads outstanding, which must then be issued whatever the rows, and behind
+    the stages: or a wavefront passes the barrier before its part of the stage has landed."""
+    name = f"mlp_block_kernelINS_6MlpCfgILi{dim}E"
+    assert name in listing
+    assert not miscounted_waits(listing, name, stage_loads)
