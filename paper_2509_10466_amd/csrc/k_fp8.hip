@@ -381,8 +381,11 @@ __global__ void __launch_bounds__(64 * NW + 64, NW == 4 ? 4 : 3) gemm_fp8_rows_k
   if (tiles) {
     if ((int)blockIdx.x >= ntiles[1]) return;
     m0 = tiles[(m_host + ROW_TILE - 1) / ROW_TILE + blockIdx.x] * ROW_TILE;
-    const int any = t < TL::BM && m0 + t < M && flag[m0 + t] != 0;
-    if (!__syncthreads_or(any)) ct0 = epi.skip() / TL::BN;
+    // (every wavefront looks for itself: a block-wide vote takes LDS, and the rows and the ring
+    // may need all of it)
+    static_assert(TL::BM == 64, "a flag per lane");
+    const bool any = m0 + lane < M && flag[min(m0 + lane, M - 1)] != 0;
+    if (__ballot(any) == 0) ct0 = epi.skip() / TL::BN;
   } else if (m0 >= M) {
     return;
   }

@@ -79,3 +79,16 @@ def test_mlp_last_block_of_any_length(net, rest):
     assert not torch.equal(alone, f[:1])
     for k in (2, n):
         assert torch.equal(eng(f[:k].contiguous(), m[:k].contiguous(), "bf16")[0], alone[0])
+
+
+@pytest.mark.parametrize("dim,ratio", [(256, 7), (640, 2), (768, 2)])
+def test_fp8_rows_of_the_wide_blocks(dim, ratio):
+    """Rows of 1,792 values (with the weight ring exactly the 160 KB of LDS), and Q/K/V and the
+    first MLP linear with rows of more than 512 values, which take the blocks of 8 + 1 wavefronts."""
+    from paper_2509_10466_amd import Inpainter
+    cfg = dataclasses.replace(MID, dim=dim, heads=dim // 64, mlp_ratio=ratio)
+    W = drsynth.make_weights(cfg, 3)
+    f, m, _ = drsynth.make_clip(6, 5, 40, 72, cov_range=(0.2, 0.4))
+    out = Inpainter(cfg, W)(torch.from_numpy(f).cuda(), torch.from_numpy(m).cuda(), "fp8").cpu().numpy()
+    compare(out, on.forward(f, m, W, cfg), f, m, TOL["fp8"])
+    assert np.isfinite(out).all()

@@ -46,7 +46,8 @@ def overwritten_operands(listing):
 
 
 @pytest.fixture(scope="module")
-def listing(tmp_path_factory):
+def objects(tmp_path_factory):
+    """print(tool, *options): the tool's text for the library's gfx950 code objects."""
     if not (OBJDUMP and os.path.exists(LIB)):
         pytest.skip("needs the built library and llvm-objdump")
     d = tmp_path_factory.mktemp("isa")
@@ -54,8 +55,14 @@ def listing(tmp_path_factory):
     subprocess.run([OBJDUMP, "--offloading", "lib.so"], cwd=d, check=True, capture_output=True)
     objs = sorted(f for f in os.listdir(d) if f.endswith("gfx950"))
     assert objs
-    return "\n".join(subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--mcpu=gfx950", f], cwd=d, check=True,
-                                    capture_output=True, text=True).stdout for f in objs)
+    return lambda tool, *options: "\n".join(
+        subprocess.run([os.path.join(os.path.dirname(OBJDUMP), tool), *options, f], cwd=d, check=True,
+                       capture_output=True, text=True).stdout for f in objs)
+
+
+@pytest.fixture(scope="module")
+def listing(objects):
+    return objects("llvm-objdump", "-d", "--no-show-raw-insn", "--mcpu=gfx950")
 
 
 def test_the_check_sees_an_overwritten_operand():
@@ -109,3 +116,13 @@ def test_mlp_stage_waits_count_what_every_wavefront_issues(listing, dim, stage_l
     name = f"mlp_block_kernelINS_6MlpCfgILi{dim}E"
     assert name in listing
     assert not miscounted_waits(listing, name, stage_loads)
+
+
+@pytest.mark.parametrize("name", ["gemm_fp8_rows_kernel", "decode_kernel"])
+def test_kernels_sized_to_the_whole_lds_have_no_fixed_part(objects, name):
+    """These are launched with up to 160 KB of dynamic LDS (FP8 rows of 1,792 values, the decoder
+    at 512 channels): any fixed part in addition makes that launch fail."""
+    notes = objects("llvm-readelf", "--notes")
+    fixed = re.findall(r"\.group_segment_fixed_size:\s+(\d+)\n(?:.*\n)*?\s+\.name:\s+(\S+)", notes)
+    sizes = {kernel: int(size) for size, kernel in fixed if name in kernel}
+    assert len(sizes) >= 5 and set(sizes.values()) == {0}, sizes
