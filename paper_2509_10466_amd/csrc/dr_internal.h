@@ -19,6 +19,13 @@ namespace dr {
 
 typedef uint16_t bf16;  // raw bfloat16 bits
 
+// Lets a kernel be launched with any dynamic LDS up to the CU's 160 KB.  For kernels whose size
+// varies between calls, called once from a static initialiser: a limit raised call by call could
+// be set back by another thread between this thread's call and its launch.
+inline bool allow_all_lds(const void* kernel) {
+  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) == hipSuccess;
+}
+
 // ------------------------------------------------------------------------------------------
 // Stages (profiling ids)
 // ------------------------------------------------------------------------------------------

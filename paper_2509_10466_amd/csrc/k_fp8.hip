@@ -485,12 +485,8 @@ static void gemm_fp8(const bf16* A, const int32_t* m_dev, int m_max, int K, int 
   const int mt = (m_max + 63) / 64;
   auto rows = [&](auto nw, int slots) {
     constexpr int NW = decltype(nw)::value;
-    static size_t granted = 0;
-    if (lds > granted) {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_fp8_rows_kernel<NW, Epi>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      granted = lds;
-    }
+    static const bool granted = allow_all_lds(reinterpret_cast<const void*>(gemm_fp8_rows_kernel<NW, Epi>));
+    (void)granted;
     const int expect = std::max(1, m_dev ? 2 * mt / 5 : mt);
     const int split = std::min(std::max(slots / expect, 1), Nout / 128);
     gemm_fp8_rows_kernel<NW, Epi><<<dim3(mt, split), 64 * NW + 64, lds, s>>>(A, m_dev, m_max, K, Nout, W, amax_a, tiles,

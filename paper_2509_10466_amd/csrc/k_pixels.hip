@@ -200,12 +200,8 @@ static void decode_launch(const Geo& g, int C, const float* x, const int32_t* id
                           const float* lnb, const float* dw, const float* db, const uint8_t* masks, float* out,
                           hipStream_t s) {
   const size_t smem = (size_t)C * (48 + NWV * TW) * sizeof(float);
-  static size_t granted = 0;
-  if (smem > granted) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(decode_kernel<NWV, TW, PER>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    granted = smem;
-  }
+  static const bool granted = allow_all_lds(reinterpret_cast<const void*>(decode_kernel<NWV, TW, PER>));
+  (void)granted;
   // eight wavefronts' rows leave room for one block per CU, which then stages the weight once
   const int grid = std::min((g.N + NWV * TW - 1) / (NWV * TW), NWV == 8 ? 256 : DEC_GRID);
   decode_kernel<NWV, TW, PER><<<grid, 64 * NWV, smem, s>>>(g, C, x, idx, nq, lng, lnb, dw, db, masks, out);

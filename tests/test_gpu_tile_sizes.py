@@ -92,3 +92,33 @@ def test_fp8_rows_of_the_wide_blocks(dim, ratio):
     out = Inpainter(cfg, W)(torch.from_numpy(f).cuda(), torch.from_numpy(m).cuda(), "fp8").cpu().numpy()
     compare(out, on.forward(f, m, W, cfg), f, m, TOL["fp8"])
     assert np.isfinite(out).all()
+
+
+def test_fp8_contexts_of_several_widths_in_threads():
+    """Four threads, each with a context and a stream of its own, run FP8 clips of widths that
+    share kernels but not LDS sizes: every result is the one of the same clip alone."""
+    import threading
+    from paper_2509_10466_amd import Inpainter
+    f, m, _ = drsynth.make_clip(7, 5, 40, 72, cov_range=(0.2, 0.4))
+    f, m = torch.from_numpy(f).cuda(), torch.from_numpy(m).cuda()
+    cfgs = [dataclasses.replace(MID, dim=d, heads=d // 64, mlp_ratio=r) for d, r in
+            ((128, 4), (256, 6), (512, 2), (768, 2))]
+    engines = [Inpainter(c, drsynth.make_weights(c, 4)) for c in cfgs]
+    torch.cuda.synchronize()
+    got, go = [[] for _ in cfgs], threading.Barrier(len(cfgs))
+
+    def work(k):
+        stream = torch.cuda.Stream()
+        go.wait()
+        with torch.cuda.stream(stream):
+            got[k] = [engines[k](f, m, "fp8") for _ in range(8)]
+        stream.synchronize()
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(cfgs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for k, eng in enumerate(engines):
+        alone = eng(f, m, "fp8")
+        assert len(got[k]) == 8 and all(torch.equal(g, alone) for g in got[k])
