@@ -130,19 +130,50 @@ __device__ __forceinline__ void ops_core(const LA& la, const LW& lw, int steps, 
   }
 }
 
-// Non-finite results of the split: recomputed with fused multiply-adds over k in order.
-// at(m, n) is the value of output (m, n) by that chain.
-template <class TL, class F>
-__device__ __forceinline__ void ops_mend(f32x4_t (&acc)[TL::FM][TL::FN], const F& at) {
+// Results of the split that are not finite (an operand, or a sum, out of range) are replaced by
+// those of fused multiply-adds over k in order; the others keep their bits.  The block computes
+// them for its whole tile, from FP32 operands in LDS: stage(step, As, Ws) writes a step's,
+// As[32][BM] and Ws[32][BN].  (A 5 x 240 x 432 clip of a 256-wide network with a NaN weight takes
+// 3.8 ms and one without 1.8; one result at a time it took 100.)
+template <class TL, class Stage>
+__device__ __forceinline__ void ops_mend(f32x4_t (&acc)[TL::FM][TL::FN], float* lds, int steps, const Stage& stage) {
   if constexpr (TL::NP == 3) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int wm = wv >> 1, wn = wv & 1, l16 = lane & 15, kg = lane >> 4;
+    f32x4_t zero = {0.f, 0.f, 0.f, 0.f};  // NaN as soon as a result is not finite
+    static_for<TL::FM>([&](auto i) {
+      static_for<TL::FN>([&](auto j) {
+        static_for<4>([&](auto e) { zero[int(e)] = fmaf(acc[i][j][int(e)], 0.f, zero[int(e)]); });
+      });
+    });
+    const bool bad = __ballot(!((zero[0] + zero[1]) + (zero[2] + zero[3]) == 0.f)) != 0;
+    if (lane == 0) lds[wv] = bad ? 1.f : 0.f;  // (every wavefront has read the last step)
+    lds_barrier();
+    if (lds[0] + lds[1] + lds[2] + lds[3] == 0.f) return;  // uniform per block
+    f32x4_t y[TL::FM][TL::FN];
+    static_for<TL::FM>([&](auto i) {
+      static_for<TL::FN>([&](auto j) { y[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; });
+    });
+    float *As = lds, *Ws = lds + 32 * TL::BM;
+    for (int step = 0; step < steps; ++step) {
+      __syncthreads();
+      stage(step, As, Ws);
+      __syncthreads();
+      for (int k = 0; k < 32; ++k) {
+        float a[TL::FM];
+        static_for<TL::FM>([&](auto i) { a[i] = As[k * TL::BM + wm * 16 * TL::FM + 16 * i + l16]; });
+        static_for<TL::FN>([&](auto j) {
+          const f32x4_t w = *reinterpret_cast<const f32x4_t*>(Ws + k * TL::BN + wn * 16 * TL::FN + 16 * j + 4 * kg);
+          static_for<TL::FM>([&](auto i) {
+            static_for<4>([&](auto e) { y[i][j][int(e)] = fmaf(a[i], w[int(e)], y[i][j][int(e)]); });
+          });
+        });
+      }
+    }
     static_for<TL::FM>([&](auto i) {
       static_for<TL::FN>([&](auto j) {
         static_for<4>([&](auto e) {
-          const float y = acc[i][j][int(e)];
-          if (!(fabsf(y) < INFINITY))
-            acc[i][j][int(e)] = at(wm * 16 * TL::FM + 16 * i + l16, wn * 16 * TL::FN + 16 * j + 4 * kg + e);
+          if (!(fabsf(acc[i][j][int(e)]) < INFINITY)) acc[i][j][int(e)] = y[i][j][int(e)];
         });
       });
     });
@@ -197,13 +228,14 @@ __global__ void __launch_bounds__(TL::THREADS, 2) gemm_ops_kernel(const float* _
   });
   f32x4_t acc[TL::FM][TL::FN];
   ops_core<TL>(la, lw, (K + 31) / 32, lds, acc);
-  ops_mend<TL>(acc, [&](int mr, int nr) {
-    const int m = m0 + mr, n = n0 + nr;
-    if (m >= M || n >= Nout) return 0.f;
-    const float *a = A + (size_t)(arows ? arows[m] : m) * K, *w = W + (size_t)n * K;
-    float y = 0.f;
-    for (int k = 0; k < K; ++k) y = fmaf(a[k], w[k], y);
-    return y;
+  ops_mend<TL>(acc, reinterpret_cast<float*>(lds), (K + 31) / 32, [&](int step, float* As, float* Ws) {
+    auto put = [&](const auto& from, auto s, int rows, float* to) {
+      float v[8];
+      from.load(step, s, v);
+      static_for<8>([&](auto e) { to[(8 * from.chunk(s) + e) * rows + from.row(s)] = v[e]; });
+    };
+    static_for<TL::SA>([&](auto s) { put(la, s, TL::BM, As); });
+    static_for<TL::SW>([&](auto s) { put(lw, s, TL::BN, Ws); });
   });
   // lane holds Y[m = .. + l16][n = .. + 4 kg + e]
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -394,13 +426,17 @@ __global__ void __launch_bounds__(TL::THREADS, 2) tn_ops_kernel(const float* __r
   const ColDma<TL::BN, TABLE> lw{B + j0, table, ldb, J - j0, m_begin, m_end - m_begin};
   f32x4_t acc[TL::FM][TL::FN];
   tn_core<TL>(la, lw, tn_lds, acc);
-  ops_mend<TL>(acc, [&](int ir, int jr) {
-    const int i = i0 + ir, j = j0 + jr;
-    if (i >= I || j >= J) return 0.f;
-    float y = 0.f;
-    for (int m = m_begin; m < m_end; ++m)
-      y = fmaf(A[(size_t)m * lda + i], B[(size_t)(TABLE ? brow[m] : m) * ldb + j], y);
-    return y;
+  ops_mend<TL>(acc, tn_lds, (m_end - m_begin + 31) / 32, [&](int step, float* As, float* Ws) {
+    auto put = [&](const float* X, int ld, const int32_t* rows, int c0, int ncol, int cols, float* to) {
+      for (int e = threadIdx.x; e < 8 * cols; e += TL::THREADS) {
+        const int r = e / (cols / 4), c = 4 * (e % (cols / 4)), m = m_begin + 32 * step + r;
+        f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+        if (m < m_end && c0 + c < ncol) v = *reinterpret_cast<const f32x4_t*>(X + (size_t)(rows ? rows[m] : m) * ld + c0 + c);
+        *reinterpret_cast<f32x4_t*>(to + r * cols + c) = v;
+      }
+    };
+    put(A, lda, nullptr, i0, I, TL::BM, As);
+    put(B, ldb, TABLE ? brow : nullptr, j0, J, TL::BN, Ws);
   });
   // lane holds P[i = .. + l16][j = .. + 4 kg + e]
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
