@@ -50,7 +50,8 @@ typedef enum {
   DR_EBUSY = 5   /* resource in use (e.g. stream id still has work in flight)              */
 } dr_status;
 
-/* Arithmetic of the attention/MLP GEMMs.  DR_FP32: plain FP32 kernels, one per operation.
+/* Arithmetic of the attention/MLP GEMMs.  DR_FP32: FP32 throughout, one kernel per
+ * operation; the linears form FP32-accurate products from three bf16 planes of each operand.
  * DR_BF16: BF16 operands on MFMA with FP32 accumulation.  DR_FP8: the Q/K/V, projection and
  * MLP GEMMs take OCP e4m3 operands with per-tensor scales (amax/448; weights fixed at load,
  * activations from the current call) and FP32 accumulation, attention stays BF16; needs dim

@@ -1,4 +1,4 @@
-// Pieces of the plain FP32 path: LayerNorm rows, and per-query window attention for the
+// Pieces of the FP32 path: LayerNorm rows, and per-query window attention for the
 // windows that the FP32 matrix-core attention (k_train_attn.hip) does not hold.  The linears
 // are in k_ops_gemm.hip.
 #include "dr_device.h"

@@ -1,4 +1,4 @@
-"""FP8 vs BF16 vs plain FP32 on the same GPU, clip mode.
+"""FP8 vs BF16 vs FP32 on the same GPU, clip mode.
 
     python -m paper_2509_10466_amd.precision_bench [--shape clip720] [--clips 3] [--steps 10]
                                                    [--attn joint|decoupled] [--overlap]
