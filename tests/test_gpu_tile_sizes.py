@@ -122,3 +122,16 @@ def test_fp8_contexts_of_several_widths_in_threads():
     for k, eng in enumerate(engines):
         alone = eng(f, m, "fp8")
         assert len(got[k]) == 8 and all(torch.equal(g, alone) for g in got[k])
+
+
+@pytest.mark.parametrize("heads", [2, 4])
+@pytest.mark.parametrize("win_h,win_w", [(16, 19), (17, 18), (16, 20)])
+def test_fp32_attention_of_the_largest_windows(win_h, win_w, heads):
+    """Windows of 304 tokens, the most that the matrix-core attention holds, and of 306 and 320,
+    which take the per-query kernel; head widths 64 and 32."""
+    from paper_2509_10466_amd import Inpainter
+    cfg = dataclasses.replace(MID, heads=heads, win_h=win_h, win_w=win_w, win_t=1)
+    W = drsynth.make_weights(cfg, 5, qk_std=0.2)
+    f, m, _ = drsynth.make_clip(8, 1, 8 * win_h, 8 * win_w, cov_range=(0.2, 0.4))
+    out = Inpainter(cfg, W)(torch.from_numpy(f).cuda(), torch.from_numpy(m).cuda(), "fp32").cpu().numpy()
+    compare(out, on.forward(f, m, W, cfg), f, m, TOL["fp32"])
