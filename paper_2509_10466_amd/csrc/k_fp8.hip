@@ -492,18 +492,21 @@ static void gemm_fp8(const bf16* A, const int32_t* m_dev, int m_max, int K, int 
     gemm_fp8_rows_kernel<NW, Epi><<<dim3(mt, split), 64 * NW + 64, lds, s>>>(A, m_dev, m_max, K, Nout, W, amax_a, tiles,
                                                                         ntiles, flag, epi);
   };
-  if constexpr (!Epi::WIDE)
+  if constexpr (!Epi::WIDE) {  // K is the network's width, at most 1,024: 112 KB
     if (K <= 512) return rows(std::integral_constant<int, 4>(), 512);
-  if (lds <= 160 * 1024) return rows(std::integral_constant<int, 8>(), 256);
-  using TL = F8Small;
-  static bool attr = false;
-  if (!attr) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_fp8_kernel<TL, Epi>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)TL::LDS_BYTES);
-    attr = true;
+    return rows(std::integral_constant<int, 8>(), 256);
+  } else {
+    if (lds <= 160 * 1024) return rows(std::integral_constant<int, 8>(), 256);
+    using TL = F8Small;
+    static bool attr = false;
+    if (!attr) {
+      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_fp8_kernel<TL, Epi>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)TL::LDS_BYTES);
+      attr = true;
+    }
+    dim3 grid((m_max + TL::BM - 1) / TL::BM, Nout / TL::BN);
+    gemm_fp8_kernel<TL, Epi><<<grid, TL::THREADS, TL::LDS_BYTES, s>>>(A, m_dev, m_max, K, W, amax_a, epi);
   }
-  dim3 grid((m_max + TL::BM - 1) / TL::BM, Nout / TL::BN);
-  gemm_fp8_kernel<TL, Epi><<<grid, TL::THREADS, TL::LDS_BYTES, s>>>(A, m_dev, m_max, K, W, amax_a, epi);
 }
 
 // x[res_rows[m], n] += s_a s_w Y + bias[n]

@@ -126,7 +126,7 @@ __global__ void __launch_bounds__(TL::THREADS, TL::BM == ROW_TILE ? 6 : 2) qkv_k
   constexpr bool ONE = SUB == 1;  // one tile per block (the grid covers them all)
   static_assert(SUB * ROW_TILE == TL::BM && SUB <= 2 && TL::ST == 2, "listed row tiles, 2-stage ring");
   static_assert(TL::BM % (8 * TL::NW) == 0 && TL::BN % (8 * TL::NW) == 0 && TL::FN % 2 == 0, "whole loads, fragment pairs");
-  static_assert(C % TL::BN == 0 && (C == 64 || C % 128 == 0), "whole column tiles; the ring half of a stage is fixed");
+  static_assert(C % TL::BN == 0 && (C % 128 == 0 || (C == 64 && ONE)), "whole column tiles; the ring half of a stage is fixed");
   extern __shared__ __align__(16) bf16 ring[];
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wv / TL::WN, wn = wv % TL::WN, l16 = lane & 15, kg = lane >> 4;
@@ -235,14 +235,9 @@ __global__ void __launch_bounds__(TL::THREADS, TL::BM == ROW_TILE ? 6 : 2) qkv_k
   read(0, I0{});
   mfma_fence_begin();
   if (nk > 1) issue(1, 1);
-  int buf = 0;  // ring half of the stage being multiplied
   for (;;) {
     const Tile nx = ONE ? Tile{total, 0, 0, 0} : find(t.slot + gridDim.x);
     const bool last = ONE || nx.slot >= total;
-    if (nk == 1 && !last) {  // the next tile's only stage (this tile's is in registers next)
-      aim(nx);
-      issue(0, buf ^ 1);
-    }
     const int part = t.n0 / C, c0 = t.n0 - part * C + wn * TL::TN + 8 * kg;
     f32x4_t bv[TL::FN];
     static_for<TL::FN>([&](auto j) {
@@ -254,6 +249,7 @@ __global__ void __launch_bounds__(TL::THREADS, TL::BM == ROW_TILE ? 6 : 2) qkv_k
     // Stage kt with its first slice read.  The stage two further on is queued once every
     // wavefront has read this one: stage kt + 2 of this tile, or of the next tile.
     auto stage = [&](int kt) {
+      const int buf = kt & 1;  // its half of the ring (a tile has an even number of stages, or is the only one)
       const bool more = kt + 1 < nk || !last;
       multiply(I0{}, [&] { read(buf, I1{}); });
       if (more) {
@@ -266,18 +262,14 @@ __global__ void __launch_bounds__(TL::THREADS, TL::BM == ROW_TILE ? 6 : 2) qkv_k
           mfma_fence_begin();
           if (kt + 2 < nk) {
             issue(kt + 2, buf);
-          } else if (!last && nk > 1) {
+          } else if (!last) {
             if (kt + 2 == nk) aim(nx);
             issue(kt + 2 - nk, buf);
           }
         }
       });
-      buf ^= 1;
     };
-    static_for<nk>([&](auto kt) {
-      if (nk > 1) buf = kt & 1;
-      stage(kt);
-    });
+    static_for<nk>([&](auto kt) { stage(kt); });
     static_for<TL::FM>([&](auto f) {
       const int m = token(t, wm * TL::TM + 16 * f + l16);
       if (m < M) {

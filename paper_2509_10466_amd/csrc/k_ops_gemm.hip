@@ -266,14 +266,6 @@ __global__ void __launch_bounds__(TL::THREADS, 2) gemm_ops_kernel(const float* _
   });
 }
 
-// dynamic LDS beyond 64 KB has to be asked for
-template <class K>
-static void ops_allow_lds(K kernel, size_t bytes) {
-  if (bytes > 65536)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)bytes);
-}
-
 // Blocks below which the 64 x 64 tile is taken: 128 x 128 tiles run two per CU, so fewer than
 // 512 of them leave CUs idle.  A row count known only on the device (the query rows) is taken
 // as 0.4 of its bound, the most a clip's mask is expected to cover.
@@ -471,8 +463,8 @@ static void tn_ops(const float* A, int lda, const float* B, const int32_t* brow,
   auto run = [&](auto tl, auto has_table) {
     using TL = decltype(tl);
     constexpr bool TABLE = decltype(has_table)::value;
+    static_assert(2 * TN_STAGE<TL> * 4 + (TABLE ? TN_CHUNK * 4 : 0) <= 65536, "more has to be asked for");
     const size_t bytes = 2 * TN_STAGE<TL> * 4 + (TABLE ? (size_t)chunk * 4 : 0);
-    ops_allow_lds(tn_ops_kernel<TL, TABLE>, bytes);
     const int tiles = ((I + TL::BM - 1) / TL::BM) * ((J + TL::BN - 1) / TL::BN);
     const int grid = 8 * ((chunks * tiles + 7) / 8);
     tn_ops_kernel<TL, TABLE><<<grid, TL::THREADS, bytes, s>>>(A, lda, B, brow, ldb, M_dev, M_max, I, J, chunk, part);
