@@ -66,6 +66,18 @@ __device__ __forceinline__ void dma16(const void* gsrc, bf16_t* lds_dst) {
   __builtin_amdgcn_global_load_lds(gsrc, (__attribute__((address_space(3))) void*)lds_dst, 16, 0, 0);
 }
 
+// A T (of 4 or 16 bytes) in LDS, read as __bf16 like the operand fragments.  Before a read that
+// may alias the destination of a direct global->LDS load still in flight the compiler waits for
+// all of them, which would undo the counted waits; destinations are bf16_t, and it holds __bf16
+// apart from that (and from int and float).  By the language this is undefined, and it is right
+// only because every such read stands behind the asm wait and barrier that make its data
+// visible, whose memory clobbers the compiler keeps in order.
+template <class T>
+__device__ __forceinline__ T lds_as_bf16(const void* p) {
+  typedef __bf16 raw_t __attribute__((ext_vector_type(sizeof(T) / 2)));
+  return __builtin_bit_cast(T, *reinterpret_cast<const raw_t*>(p));
+}
+
 template <int BM_, int BN_, int WM_, int WN_, int ST_>
 struct GemmTile {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, ST = ST_;

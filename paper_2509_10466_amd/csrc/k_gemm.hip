@@ -941,8 +941,8 @@ __device__ __forceinline__ void mlp_block(int M, const bf16* __restrict__ o, con
   static_for<MC::NCH>([&](auto j) {
     // the chunk's accumulators start at its bias b1' (the GELU epilogue then adds nothing)
     static_for<MC::FN_H>([&](auto jj) {
-      const bf16x8_t b4 = *reinterpret_cast<const bf16x8_t*>(sb1 + j * HC + wn * 16 * MC::FN_H + 16 * jj + 4 * kg);
-      static_for<MC::FM>([&](auto i) { hacc[i][jj] = __builtin_bit_cast(f32x4_t, b4); });
+      const f32x4_t b4 = lds_as_bf16<f32x4_t>(sb1 + j * HC + wn * 16 * MC::FN_H + 16 * jj + 4 * kg);
+      static_for<MC::FM>([&](auto i) { hacc[i][jj] = b4; });
     });
     constexpr int s1 = S1 + j * MC::PER_CHUNK, s2 = s1 + MC::NW1;
     // (the last W1' stage enters the first W_2 stage, whose H rows do not exist yet)

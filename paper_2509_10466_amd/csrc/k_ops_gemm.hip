@@ -324,7 +324,7 @@ struct ColDma {
       bf16_t* to = reinterpret_cast<bf16_t*>(dst + first(i) * COLS);
       if constexpr (TABLE) {
         const int m = min(32 * step + row(i), count - 1);
-        const int r = __builtin_bit_cast(int, *reinterpret_cast<const bf16x2_t*>(rows + m));
+        const int r = lds_as_bf16<int>(rows + m);
         dma16(X + (size_t)r * ld + col(i), to);
       } else if (32 * step + 32 <= count) {  // a uniform base and a lane's offset, the same in every step
         dma16(X + (size_t)(m_begin + 32 * step) * ld + ((uint32_t)row(i) * ld + col(i)), to);
@@ -337,8 +337,7 @@ struct ColDma {
   template <class Full>
   __device__ __forceinline__ static void get(Full full, const float* src, int kg, int c, int left, float (&v)[8]) {
     static_for<8>([&](auto e) {
-      const float x = __builtin_bit_cast(
-          float, *reinterpret_cast<const bf16x2_t*>(src + (8 * kg + e) * COLS + (c ^ (16 * kg))));
+      const float x = lds_as_bf16<float>(src + (8 * kg + e) * COLS + (c ^ (16 * kg)));
       v[e] = full || 8 * kg + e < left ? x : 0.f;
     });
   }
