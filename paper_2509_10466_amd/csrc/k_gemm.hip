@@ -410,8 +410,10 @@ void launch_fc1_bf16(int m_max, const int32_t* m_dev, int C, int R, const bf16* 
   if (m_max <= 0) return;
   if (m_max >= BIG_M && R % 256 == 0)
     fc1_launch<GemmTile<128, 256, 2, 4, 2>>(m_max, m_dev, C, R, u2, w, bias, h, s);
-  else
+  else if (R % 128 == 0)
     fc1_launch<GemmTile<64, 128, 2, 2, 2>>(m_max, m_dev, C, R, u2, w, bias, h, s);
+  else  // dim 64 with an odd MLP ratio
+    fc1_launch<GemmTile<64, 64, 2, 2, 3>>(m_max, m_dev, C, R, u2, w, bias, h, s);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -135,3 +135,15 @@ def test_fp32_attention_of_the_largest_windows(win_h, win_w, heads):
     f, m, _ = drsynth.make_clip(8, 1, 8 * win_h, 8 * win_w, cov_range=(0.2, 0.4))
     out = Inpainter(cfg, W)(torch.from_numpy(f).cuda(), torch.from_numpy(m).cuda(), "fp32").cpu().numpy()
     compare(out, on.forward(f, m, W, cfg), f, m, TOL["fp32"])
+
+
+@pytest.mark.parametrize("ratio", [1, 3, 5])
+def test_bf16_hidden_widths_of_the_narrowest_network(ratio):
+    """Dim 64 with an odd MLP ratio: hidden widths of 64, 192 and 320 are no multiple of the 128
+    columns that the first MLP linear's tiles have otherwise."""
+    from paper_2509_10466_amd import Inpainter
+    cfg = dataclasses.replace(drsynth.NETS["tiny64"], mlp_ratio=ratio)
+    W = drsynth.make_weights(cfg, 6, std=0.1)
+    f, m = drsynth.tiny_frame(9)
+    out = Inpainter(cfg, W)(torch.from_numpy(f).cuda(), torch.from_numpy(m).cuda(), "bf16").cpu().numpy()
+    compare(out, on.forward(f, m, W, cfg), f, m, TOL["bf16"])
