@@ -204,8 +204,8 @@ void launch_ln_rows_amax(const float* x, const int32_t* rows, const int32_t* nro
 // else m_host.
 //
 // gemm_fp8_rows_kernel: a block holds 64 rows of A in LDS, quantised once, and runs column
-// tiles of 128 (all of them, or a share where there are too few row tiles to fill the chip:
-// blockIdx.y of gridDim.y) with the weight streaming through a 3-stage ring of 128-wide k
+// tiles of 128 (all of them, or a share where there are too few row tiles to fill the chip) with
+// the weight streaming through a 3-stage ring of 128-wide k
 // stages by direct global->LDS loads.  (A 64 x 128 tile per block quantised its A rows again
 // for every column tile, through registers, and the weight too: 450 us for Q/K/V and 232 us
 // for the first MLP linear at 5 x 720 x 1280, against about 140 and 70 us for their bytes.)
@@ -356,7 +356,13 @@ struct F8Rows {
 static_assert(F8Rows<4>::BM == ROW_TILE, "row tiles are listed in ROW_TILE units");
 
 // With lists (Q/K/V: K/V row tiles listed with the window order, their Q columns only where a
-// token of the tile is flagged) block x takes listed tile x, else rows 64 x ..
+// token of the tile is flagged) row tile i is listed tile i, else rows 64 i ..
+//
+// How many row tiles there are is known here, not at the launch: with few of them (a clip with
+// few masked tokens) their column tiles are shared by as many blocks as give one round of
+// `slots` blocks.  (With the share fixed at the launch for 0.4 of the tokens, clips with 2 % of
+// their tokens masked took up to a third longer: 5 x 240 x 432 at 768 channels, two blocks,
+// 376 -> 514 us, 275 now.)
 //
 // The weight is queued by a wavefront of its own (the last), which waits for its loads alone:
 // vector-memory operations complete in order for a wavefront's counter, so a wavefront that
@@ -364,7 +370,7 @@ static_assert(F8Rows<4>::BM == ROW_TILE, "row tiles are listed in ROW_TILE units
 template <int NW, class Epi>
 __global__ void __launch_bounds__(64 * NW + 64, NW == 4 ? 4 : 3) gemm_fp8_rows_kernel(const bf16* __restrict__ A,
                                                                 const int32_t* __restrict__ m_dev, int m_host, int K,
-                                                                int Nout, const uint8_t* __restrict__ W,
+                                                                int Nout, int slots, const uint8_t* __restrict__ W,
                                                                 const float* __restrict__ amax_a,
                                                                 const int32_t* __restrict__ tiles,
                                                                 const int32_t* __restrict__ ntiles,
@@ -377,20 +383,25 @@ __global__ void __launch_bounds__(64 * NW + 64, NW == 4 ? 4 : 3) gemm_fp8_rows_k
   const int M = m_dev ? m_dev[0] : m_host;
   const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wm = wv / TL::WN, wn = wv % TL::WN, l16 = lane & 15, kg = lane >> 4;
-  int m0 = blockIdx.x * TL::BM, ct0 = 0;
+  const int nrt = tiles ? ntiles[1] : (M + TL::BM - 1) / TL::BM;
+  int rt = blockIdx.x, share = 0, shares = 1;
+  if (nrt > 0 && 2 * nrt <= slots) {
+    shares = min(slots / nrt, Nout / TL::BN);
+    share = rt / nrt;
+    rt -= share * nrt;
+  }
+  if (rt >= nrt || share >= shares) return;
+  int m0 = rt * TL::BM, ct0 = 0;
   if (tiles) {
-    if ((int)blockIdx.x >= ntiles[1]) return;
-    m0 = tiles[(m_host + ROW_TILE - 1) / ROW_TILE + blockIdx.x] * ROW_TILE;
+    m0 = tiles[(m_host + ROW_TILE - 1) / ROW_TILE + rt] * ROW_TILE;
     // (every wavefront looks for itself: a block-wide vote takes LDS, and the rows and the ring
     // may need all of it)
     static_assert(TL::BM == 64, "a flag per lane");
     const bool any = m0 + lane < M && flag[min(m0 + lane, M - 1)] != 0;
     if (__ballot(any) == 0) ct0 = epi.skip() / TL::BN;
-  } else if (m0 >= M) {
-    return;
   }
   const int nct = Nout / TL::BN - ct0;
-  const int first = ct0 + nct * blockIdx.y / gridDim.y, last = ct0 + nct * (blockIdx.y + 1) / gridDim.y;
+  const int first = ct0 + nct * share / shares, last = ct0 + nct * (share + 1) / shares;
   const int total = (last - first) * nk;  // weight stages
   if (total <= 0) return;
   if (wv == NW) {  // the loader: barrier k opens stage k, behind which slot k - 1 is free
@@ -474,8 +485,8 @@ __global__ void __launch_bounds__(64 * NW + 64, NW == 4 ? 4 : 3) gemm_fp8_rows_k
 
 // The row kernel while its A rows and ring fit the LDS: two blocks of 4 + 1 wavefronts per CU to
 // K = 512 (both have their fifth wavefront on the same SIMD, so 128 registers), then, and for
-// the residual epilogue, which needs more registers, blocks of 8 + 1.  The column tiles are shared by as many blocks as it takes to have one
-// round of them (a row count known only on the device is taken as 0.4 of its bound).
+// the residual epilogue, which needs more registers, blocks of 8 + 1.  The grid covers every row
+// tile there can be, and one round of blocks where column tiles may be shared.
 template <class Epi>
 static void gemm_fp8(const bf16* A, const int32_t* m_dev, int m_max, int K, int Nout, const uint8_t* W,
                      const float* amax_a, const Epi& epi, hipStream_t s, const int32_t* tiles = nullptr,
@@ -487,10 +498,9 @@ static void gemm_fp8(const bf16* A, const int32_t* m_dev, int m_max, int K, int 
     constexpr int NW = decltype(nw)::value;
     static const bool granted = allow_all_lds(reinterpret_cast<const void*>(gemm_fp8_rows_kernel<NW, Epi>));
     (void)granted;
-    const int expect = std::max(1, m_dev ? 2 * mt / 5 : mt);
-    const int split = std::min(std::max(slots / expect, 1), Nout / 128);
-    gemm_fp8_rows_kernel<NW, Epi><<<dim3(mt, split), 64 * NW + 64, lds, s>>>(A, m_dev, m_max, K, Nout, W, amax_a, tiles,
-                                                                        ntiles, flag, epi);
+    const int grid = (int)std::max<long long>(mt, std::min<long long>(slots, (long long)mt * (Nout / 128)));
+    gemm_fp8_rows_kernel<NW, Epi><<<grid, 64 * NW + 64, lds, s>>>(A, m_dev, m_max, K, Nout, slots, W, amax_a, tiles,
+                                                                  ntiles, flag, epi);
   };
   if constexpr (!Epi::WIDE) {  // K is the network's width, at most 1,024: 112 KB
     if (K <= 512) return rows(std::integral_constant<int, 4>(), 512);
